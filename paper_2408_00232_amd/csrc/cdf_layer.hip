@@ -48,9 +48,9 @@ static size_t max_sz(size_t a, size_t b) { return a > b ? a : b; }
 // ---- per-kernel timing: one (start, stop) event pair per launch, kept in launch order ----
 static const char* const kKernelNames[K_COUNT] = {
     "filter_kernel", "scan_kernel", "compact_kernel", "quantize_kernel", "dequantize_kernel",
-    "chunk_rows_kernel", "spmm_kernel", "spmm_fixup_kernel", "gemm_kernel<FWD>", "gemm_kernel<DW>",
-    "reduce_slabs_kernel", "gemm_kernel<DM>", "spmm_sliced_kernel", "relu_mask_kernel", "test_encode_kernel",
-    "gather_codes_kernel", "spmm_kernel<transform>"};
+    "chunk_rows_kernel", "spmm_fixup_kernel", "gemm_kernel<FWD>", "gemm_kernel<DW>",
+    "reduce_slabs_kernel", "gemm_kernel<DM>", "spmm_walk_kernel", "relu_mask_kernel", "test_encode_kernel",
+    "gather_codes_kernel", "spmm_transform_kernel"};
 constexpr int kProfCap = 8192;
 struct ProfRec {
   int id;

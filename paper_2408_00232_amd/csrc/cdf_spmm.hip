@@ -4,23 +4,21 @@
 // Work split: the stored entries are cut into chunks of 64 to 1024 consecutive entries and
 // each wavefront takes one chunk, whatever rows it covers - a power-law degree
 // distribution (rows of 1 to several 10^5 entries) therefore loads every wavefront
-// equally. Inside a chunk the wavefront walks the entries in storage order: the 64
-// lanes first fetch 64 (column, value) pairs with one coalesced load each, then the
-// entries' feature rows are gathered, several gather instructions in flight at a time,
-// and accumulated in fp32 registers. Row ends are wave-uniform: at a row end the
-// accumulator is stored as one coalesced row of Y.
-//
-// Two kernels. spmm_kernel gives the whole wavefront to one entry at a time (lane l reads
-// elements [l*EPV, l*EPV+EPV) of each 64*EPV-wide pass; column ids and values reach all lanes
-// through v_readlane). spmm_sliced_kernel gives LPR lanes to an entry, so one gather
-// instruction serves 64 / LPR entries: rows of whole 128-byte lines are processed in vertical
-// slices of one line (LPR = 8), rows of at most 32 lane-vectors in one slice whose lane group is
-// just wide enough for the row (LPR = 2 ... 32).
+// equally. Inside a chunk the wavefront's lane groups walk one run of consecutive entries each
+// (spmm_walk_kernel); several gather instructions are in flight at a time and the sums are kept
+// in fp32 registers.
 //
 // Rows that straddle chunk borders: the piece at the start of a chunk that continues an
 // earlier row goes to phead[chunk], the piece at the end of a chunk that continues into
 // the next goes to ptail[chunk] (both fp32); a second kernel adds a row's pieces in
-// chunk order and writes the row once. No atomics: results are bit-reproducible.
+// chunk order and writes the row once. No atomics on results: they are bit-reproducible.
+//
+// spmm_transform_kernel is the aggregation with the dense transform in its row epilogue: the
+// whole wavefront takes one entry at a time (lane l reads elements [l*EPV, l*EPV+EPV) of each
+// 64*EPV-wide pass; column ids and values reach all lanes through v_readlane), so that a finished
+// row is whole in one wavefront.
+#include <type_traits>
+
 #include "cdf_common.h"
 
 namespace cdf {
@@ -71,10 +69,10 @@ __device__ __forceinline__ void transform_row(const float* row, const float* W, 
 // LDS of the transforming variants: W, then one row buffer per wavefront (rows padded to 4 floats)
 __host__ __device__ inline int xf_row_floats(int dim) { return (dim + 3) / 4 * 4; }
 
-template <typename T, int EPV, int NP, bool XF = false>
-__global__ __launch_bounds__(kSpmmThreads) void spmm_kernel(
+template <typename T, int EPV, int NP>
+__global__ __launch_bounds__(kSpmmThreads) void spmm_transform_kernel(
     const int64_t* __restrict__ rowptr, const int* __restrict__ colidx, const float* __restrict__ vals,
-    int n_rows, int64_t nnz, const T* __restrict__ X, int64_t ldx, T* __restrict__ Y, T* __restrict__ Y2,
+    int n_rows, int64_t nnz, const T* __restrict__ X, int64_t ldx, T* __restrict__ Y,
     int64_t ldy, int dim, const int* __restrict__ chunk_row, int64_t nchunks, float* __restrict__ phead, float* __restrict__ ptail,
     int* __restrict__ tail_row, int kChunk, XformArgs xf) {
   constexpr int U = (8 / NP) > 0 ? (8 / NP) : 1;  // feature rows in flight per wavefront
@@ -83,10 +81,8 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_kernel(
   // the wavefront index is the same in all lanes: say so, and everything derived from it
   // (chunk bounds, row cursor, loop counters) lives in scalar registers
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if constexpr (XF) {
-    for (int i = threadIdx.x; i < dim * xf.G; i += kSpmmThreads) xf_lds[i] = xf.W[i];
-    __syncthreads();
-  }
+  for (int i = threadIdx.x; i < dim * xf.G; i += kSpmmThreads) xf_lds[i] = xf.W[i];
+  __syncthreads();
   const int64_t chunk = static_cast<int64_t>(blockIdx.x) * kSpmmWaves + wave;
   if (chunk >= nchunks) return;
   const int64_t s = chunk * kChunk;
@@ -128,40 +124,25 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_kernel(
     }
     cur_end = __builtin_amdgcn_readlane(rel, r - r_base);
   };
-  // a finished row: Y gets the sum (if wanted), Y2 its positive part (if wanted)
+  // a finished row: stored, then transformed
   auto store_y = [&](int row) {
-    if (Y) {
-      T* py = Y + static_cast<int64_t>(row) * ldy;
+    T* py = Y + static_cast<int64_t>(row) * ldy;
 #pragma unroll
-      for (int p = 0; p < NP; ++p)
-        if (col_on[p]) VecIO<T, EPV>::store(py + (p * 64 + lane) * EPV, acc[p]);
-    }
-    if (Y2) {
-      T* py = Y2 + static_cast<int64_t>(row) * ldy;
+    for (int p = 0; p < NP; ++p)
+      if (col_on[p]) VecIO<T, EPV>::store(py + (p * 64 + lane) * EPV, acc[p]);
+    // the row goes to this wavefront's LDS buffer, then every lane < G forms one output
+    float* rb = xf_lds + xf_row_floats(dim * xf.G) + wave * xf_row_floats(dim);
 #pragma unroll
-      for (int p = 0; p < NP; ++p)
-        if (col_on[p]) {
-          float pos[EPV];
+    for (int p = 0; p < NP; ++p)
+      if (col_on[p]) {
 #pragma unroll
-          for (int c = 0; c < EPV; ++c) pos[c] = acc[p][c] > 0.0f ? acc[p][c] : 0.0f;
-          VecIO<T, EPV>::store(py + (p * 64 + lane) * EPV, pos);
-        }
-    }
-    if constexpr (XF) {
-      // the finished row goes to this wavefront's LDS buffer, then every lane < G forms one output
-      float* rb = xf_lds + xf_row_floats(dim * xf.G) + wave * xf_row_floats(dim);
-#pragma unroll
-      for (int p = 0; p < NP; ++p)
-        if (col_on[p]) {
-#pragma unroll
-          for (int c = 0; c < EPV; ++c) rb[(p * 64 + lane) * EPV + c] = acc[p][c];
-        }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      transform_row(rb, xf_lds, dim, xf, row, lane);
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the next row is written only after every lane has read this one
-    }
+        for (int c = 0; c < EPV; ++c) rb[(p * 64 + lane) * EPV + c] = acc[p][c];
+      }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    transform_row(rb, xf_lds, dim, xf, row, lane);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the next row is written only after every lane has read this one
   };
   auto store_partial = [&](float* buf) {
     float* pp = buf + chunk * static_cast<int64_t>(dim);
@@ -253,243 +234,343 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_kernel(
   if (lane == 0) tail_row[chunk] = tr;
 }
 
-// Column-sliced variant for rows that are several cache lines wide. The feature matrix is
-// processed in vertical slices of SW = LPR * EPV elements (grid.y = slice); within a slice a
-// gather instruction serves 64 / LPR stored entries at once, LPR lanes each. Narrow slices shrink
-// the table the gathers hit by dim / SW, so far more of its rows stay in the 4 MB L2 of an XCD
-// and in the memory-side cache; the CSR arrays are re-read once per slice (8 bytes per entry
-// against SW * 4 of features). Entries of a row are spread round-robin over the lane groups and
-// the groups' partial sums are combined when the row ends - a fixed order, no atomics.
-template <typename T, int EPV, int LPR, int UREQ>
-__global__ __launch_bounds__(kSpmmThreads) void spmm_sliced_kernel(
+// ---- the aggregation kernel ------------------------------------------------------------------------
+// A lane group of LPR lanes walks its own run of consecutive stored entries: one gather instruction then
+// serves 64 / LPR entries of 64 / LPR runs, each lane holding EPV columns of its run's open row. grid.y
+// cuts the feature matrix into vertical slices of LPR * EPV columns.
+//
+// What bounds it: the gathered lines - the L2 <-> fabric interface where the table exceeds the caches, the
+// instruction stream where it does not. A group owns its run, so an entry costs a gather, EPV multiply-adds
+// and one test of a bit: no masks and no exchange between groups at a row end (a row that ends in the middle
+// of a run is stored by its group alone; what crosses runs is combined once per chunk). With groups sharing a
+// window of 64 entries and exchanging partial sums at every row end, the kernel before this one took 185 / 200
+// us at 256 floats a row on 1.8 M entries (matrix / transpose), 539 / 353 us at 602, 74 / 76 us at 41, and 4.6 ms on
+// 49 M entries that hit the caches; this one takes 100 / 89, 373 / 224, 33 / 31 us and 3.2 ms. On matrices far
+// larger than the caches (144 M entries, 256 floats) both take 21 ms.
+// A lane fetches four (column, value) pairs at a time, a group therefore whole lines of the CSR arrays: fetched
+// eight entries at a time those lines were requested four times over (23.0 against 21.7 ms on that matrix).
+// EPV elements of T from any element-aligned address (global memory takes 16-byte accesses there).
+template <typename T, int EPV>
+struct RawVec;
+template <>
+struct RawVec<float, 4> {
+  typedef float v_t __attribute__((ext_vector_type(4), aligned(4)));
+  v_t v;
+  __device__ __forceinline__ void load(const float* p) { v = *reinterpret_cast<const v_t*>(p); }
+  __device__ __forceinline__ void fma_into(float w, float (&acc)[4]) const {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[c] = __fmaf_rn(w, v[c], acc[c]);
+  }
+  static __device__ __forceinline__ void store(float* p, const float (&a)[4]) {
+    *reinterpret_cast<v_t*>(p) = v_t{a[0], a[1], a[2], a[3]};
+  }
+};
+template <>
+struct RawVec<bf16_t, 8> {
+  typedef uint32_t v_t __attribute__((ext_vector_type(4), aligned(2)));
+  v_t v;
+  __device__ __forceinline__ void load(const bf16_t* p) { v = *reinterpret_cast<const v_t*>(p); }
+  __device__ __forceinline__ void fma_into(float w, float (&acc)[8]) const {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      acc[2 * c] = __fmaf_rn(w, __uint_as_float(v[c] << 16), acc[2 * c]);
+      acc[2 * c + 1] = __fmaf_rn(w, __uint_as_float(v[c] & 0xffff0000u), acc[2 * c + 1]);
+    }
+  }
+  static __device__ __forceinline__ void store(bf16_t* p, const float (&a)[8]) {
+    v_t t;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) t[c] = f2bf(a[2 * c]) | (static_cast<uint32_t>(f2bf(a[2 * c + 1])) << 16);
+    *reinterpret_cast<v_t*>(p) = t;
+  }
+};
+template <typename T>
+struct RawVec<T, 1> {
+  T v;
+  __device__ __forceinline__ void load(const T* p) { v = *p; }
+  __device__ __forceinline__ void fma_into(float w, float (&acc)[1]) const {
+    float x[1];
+    VecIO<T, 1>::load(&v, x);
+    acc[0] = __fmaf_rn(w, x[0], acc[0]);
+  }
+  static __device__ __forceinline__ void store(T* p, const float (&a)[1]) { VecIO<T, 1>::store(p, a); }
+};
+
+constexpr int kWalkBlock = 8;   // entries of a run fetched together (8 gathers in flight per lane)
+
+// LDS ints per wavefront: a bit per entry of the chunk (last of its row), and that row's number
+__host__ __device__ constexpr int walk_lds_ints(int chunk) { return chunk / 32 + chunk; }
+
+template <typename T, int EPV, int LPR, bool QUAD>
+__global__ __launch_bounds__(kSpmmThreads) void spmm_walk_kernel(
     const int64_t* __restrict__ rowptr, const int* __restrict__ colidx, const float* __restrict__ vals,
-    int n_rows, int64_t nnz, const T* __restrict__ X, int64_t ldx, T* __restrict__ Y, T* __restrict__ Y2,
-    int64_t ldy, int dim, const int* __restrict__ chunk_row, int64_t nchunks, float* __restrict__ phead,
+    int n_rows, int64_t nnz, const T* __restrict__ X, uint64_t ldx, T* __restrict__ Y, T* __restrict__ Y2,
+    int64_t ldy, int dim, const int* __restrict__ chunk_row, int plan_step, int64_t nchunks, float* __restrict__ phead,
     float* __restrict__ ptail, int* __restrict__ tail_row, int kChunk) {
-  constexpr int EPI = 64 / LPR;  // stored entries per gather instruction
-  constexpr int SW = LPR * EPV;  // slice width in elements
-  constexpr int U = UREQ * EPI > 64 ? 64 / EPI : UREQ;  // gather instructions in flight (a window holds 64 entries)
+  constexpr int NG = 64 / LPR;
+  constexpr int KB = kWalkBlock;
+  // (column, value) pairs a lane fetches at a time, and entries of its run that its group then holds
+  constexpr int NLD = QUAD ? 4 : LPR >= KB ? 1 : KB / LPR;
+  constexpr int HOLD = QUAD ? 4 * LPR : KB;
+  constexpr bool kAnyPitch = EPV == 1;            // the other instances multiply 32-bit factors
+  extern __shared__ int walk_lds[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t chunk = static_cast<int64_t>(blockIdx.x) * kSpmmWaves + wave;
   if (chunk >= nchunks) return;
   const int g = lane / LPR, lg = lane % LPR;
-  const int col0 = blockIdx.y * SW + lg * EPV;  // this lane's columns: [col0, col0 + EPV)
-  const bool lane_on = col0 < dim;              // false on the lanes past the row end in a partial last slice
+  // this lane's columns; lanes past the row end take the row's last EPV columns once more (same sums, same stores)
+  const int col0 = min(static_cast<int>(blockIdx.y) * (LPR * EPV) + lg * EPV, dim - EPV);
   const int64_t s = chunk * kChunk;
   const int L = static_cast<int>(nnz - s < kChunk ? nnz - s : kChunk);
-  int my_col = 0, krel = 0;
-  float my_val = 0.0f;
+  unsigned* ends = reinterpret_cast<unsigned*>(walk_lds + wave * walk_lds_ints(kChunk));
+  int* row_of = reinterpret_cast<int*>(ends) + kChunk / 32;
 
-  int r = chunk == 0 ? 0 : chunk_row[chunk];
-  bool head = chunk > 0 && rowptr[r] < s;
-  auto load_rel = [&](int rbase) -> int {
-    const int rr = rbase + lane;
-    if (rr < n_rows) {
-      const int64_t d = rowptr[rr + 1] - s;
-      return d > kChunk ? kChunk + 1 : static_cast<int>(d);
-    }
-    return kChunk + 2;
-  };
-  int r_base = r;
-  int rel = load_rel(r_base);
-  int cur_end = __builtin_amdgcn_readlane(rel, 0);
-  auto next_row = [&]() {
-    ++r;
-    if (r - r_base == 64) {
-      r_base = r;
-      rel = load_rel(r_base);
-    }
-    cur_end = __builtin_amdgcn_readlane(rel, r - r_base);
-  };
-
-  float acc[EPV];
-#pragma unroll
-  for (int c = 0; c < EPV; ++c) acc[c] = 0.0f;
-
-  // Combine the lane groups' sums with a halving exchange: at stride 32, 16, ..., LPR each lane
-  // passes one half of its components to its partner and adds the partner's other half, so the
-  // row slice ends up spread over the lanes (FIN components each, starting at component cbase)
-  // with a quarter of the shuffles of a full butterfly. Once a lane is down to one component the
-  // remaining strides are plain sums and only the lanes with the stride bit clear keep the result.
-  constexpr int FIN = EPV / EPI > 0 ? EPV / EPI : 1;
-  int cbase = 0;       // first component (within this lane's EPV) that the lane owns after the exchange
-  bool owner = true;   // false on lanes that hold a duplicate
-  {
-    int cnt = EPV;
-#pragma unroll
-    for (int off = 32; off >= LPR; off >>= 1) {
-      const bool up = (lane & off) != 0;
-      if (cnt > 1) {
-        cnt >>= 1;
-        if (up) cbase += cnt;
-      } else if (up) {
-        owner = false;
-      }
-    }
-  }
-  auto reduce_groups = [&](float (&fin)[FIN]) {
-    float a[EPV];
-#pragma unroll
-    for (int c = 0; c < EPV; ++c) a[c] = acc[c];
-    int cnt = EPV;
-#pragma unroll
-    for (int off = 32; off >= LPR; off >>= 1) {
-      const bool up = (lane & off) != 0;
-      if (cnt > 1) {
-        const int half = cnt >> 1;
-#pragma unroll
-        for (int i = 0; i < EPV / 2; ++i) {
-          if (i < half) {
-            const float send = up ? a[i] : a[half + i];
-            const float keep = up ? a[half + i] : a[i];
-            a[i] = keep + __shfl_xor(send, off, kWave);
-          }
-        }
-        cnt = half;
-      } else {
-        a[0] = a[0] + __shfl_xor(a[0], off, kWave);
-      }
-    }
-#pragma unroll
-    for (int c = 0; c < FIN; ++c) fin[c] = a[c];
-  };
-  auto store_y = [&](int row, const float (&fin)[FIN]) {
-    if (!owner || !lane_on) return;
-    const int64_t at = static_cast<int64_t>(row) * ldy + col0 + cbase;
-    if (Y) VecIO<T, FIN>::store(Y + at, fin);
+  auto store_row = [&](int row, const float (&a)[EPV]) {
+    const uint64_t at = (kAnyPitch ? static_cast<uint64_t>(row) * static_cast<uint64_t>(ldy)
+                                   : static_cast<uint64_t>(static_cast<uint32_t>(row)) * static_cast<uint32_t>(ldy)) + col0;
+    if (Y) RawVec<T, EPV>::store(Y + at, a);
     if (Y2) {
-      float pos[FIN];
+      float pos[EPV];
 #pragma unroll
-      for (int c = 0; c < FIN; ++c) pos[c] = fin[c] > 0.0f ? fin[c] : 0.0f;
-      VecIO<T, FIN>::store(Y2 + at, pos);
+      for (int c = 0; c < EPV; ++c) pos[c] = a[c] > 0.0f ? a[c] : 0.0f;
+      RawVec<T, EPV>::store(Y2 + at, pos);
     }
   };
-  auto store_partial = [&](float* buf, const float (&fin)[FIN]) {
-    if (!owner || !lane_on) return;
-    float* pp = buf + chunk * static_cast<int64_t>(dim) + col0 + cbase;
+  auto store_piece = [&](float* buf, const float (&a)[EPV]) {
+    float* p = buf + chunk * static_cast<int64_t>(dim) + col0;
+    if constexpr (EPV == 1) {
+      *p = a[0];
+    } else {
 #pragma unroll
-    for (int c = 0; c < FIN; ++c) pp[c] = fin[c];
+      for (int h = 0; h < EPV; h += 4) {
+        const float q[4] = {a[h], a[h + 1], a[h + 2], a[h + 3]};
+        RawVec<float, 4>::store(p + h, q);
+      }
+    }
   };
-  auto flush_row = [&]() {
-    float fin[FIN];
-    reduce_groups(fin);
-    if (head) store_partial(phead, fin);
-    else store_y(r, fin);
-    head = false;
+
+  // ---- where rows end inside the chunk ----
+  for (int w = lane; w < kChunk / 32; w += 64) ends[w] = 0u;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  const int r0 = chunk == 0 ? 0 : chunk_row[chunk * plan_step];
+  bool head = false;   // the chunk's first row began in an earlier chunk
+  int tr = -1;         // row that runs on past the chunk
+  for (int base = r0;; base += 64) {
+    const int rr = base + lane;
+    const bool in = rr < n_rows;
+    const int64_t d0 = in ? rowptr[rr] - s : kChunk + 1, d1 = in ? rowptr[rr + 1] - s : kChunk + 1;
+    const int e0 = d0 < 0 ? -1 : d0 > kChunk ? kChunk + 1 : static_cast<int>(d0);
+    const int e1 = d1 > kChunk ? kChunk + 1 : static_cast<int>(d1);
+    if (base == r0) head = __builtin_amdgcn_readfirstlane(e0) < 0;
+    if (in && e1 > e0 && e1 <= L) {
+      atomicOr(&ends[(e1 - 1) >> 5], 1u << ((e1 - 1) & 31));
+      row_of[e1 - 1] = rr;
+    }
+    const unsigned long long on = __ballot(in && e0 < L && e1 > L);
+    if (on != 0ull) tr = base + __builtin_ctzll(on);
+    // rows without entries: the chunk that holds the entry before them writes their zeros
+    unsigned long long empty = __ballot(in && e0 == e1 && e0 <= L && (e0 > 0 || chunk == 0));
+    while (empty != 0ull) {
+      unsigned long long m = empty;   // group g takes the g-th of the next NG empty rows
+      int mine = -1;
+#pragma unroll 1
+      for (int q = 0; q < NG && m != 0ull; ++q) {
+        if (q == g) mine = base + __builtin_ctzll(m);
+        m &= m - 1;
+      }
+      empty = m;
+      float zero[EPV];
 #pragma unroll
-    for (int c = 0; c < EPV; ++c) acc[c] = 0.0f;
-  };
+      for (int c = 0; c < EPV; ++c) zero[c] = 0.0f;
+      if (mine >= 0) store_row(mine, zero);
+    }
+    if (__ballot(!in || e1 > L) != 0ull) break;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+
+  // ---- every lane group walks its run of the chunk ----
+  const int run = kChunk / NG;      // a multiple of KB
+  const int beg = g * run;
+  bool open = g == 0 ? head : ((ends[(beg - 1) >> 5] >> ((beg - 1) & 31)) & 1u) == 0u;   // run starts inside a row
+  bool ended = false;               // a row ended inside this run
+  int first_row = 0;                // the first one, if it began before the run: its part is kept aside
+  float acc[EPV], first[EPV];
+#pragma unroll
+  for (int c = 0; c < EPV; ++c) acc[c] = first[c] = 0.0f;
 
   const T* xs = X + col0;
-  for (int base = 0; base < L; base += 64) {
-    const int cnt = L - base < 64 ? L - base : 64;
-    my_col = 0;
-    my_val = 0.0f;
-    if (lane < cnt) {
-      my_col = colidx[s + base + lane];
-      my_val = vals[s + base + lane];
-    }
-    for (int j = 0; j < cnt; j += EPI * U) {
-      float x[U][EPV];
-      float v[U];
+  const int* cp = colidx + s + beg;
+  const float* vp = vals + s + beg;
+  // entries k .. k + HOLD - 1 of the run: lane lg holds NLD consecutive ones (or, where a group is wider than a
+  // block, lane lg % KB holds one)
+  int col[NLD];
+  float val[NLD];
+  auto fetch = [&](int k0, auto full) {
+    const int k = k0 + (NLD > 1 ? lg * NLD : lg % KB);
+    if constexpr (decltype(full)::value && NLD == 4) {
+      typedef int i4u __attribute__((ext_vector_type(4), aligned(4)));
+      typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+      const i4u c = *reinterpret_cast<const i4u*>(cp + k);
+      const f4u v = *reinterpret_cast<const f4u*>(vp + k);
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int e = j + u * EPI + g;  // this group's entry of instruction u
-        const int c = __shfl(my_col, e, kWave);
-        v[u] = __shfl(my_val, e, kWave);
-#pragma unroll
-        for (int q = 0; q < EPV; ++q) x[u][q] = 0.0f;
-        if (e < cnt && lane_on) VecIO<T, EPV>::load(xs + static_cast<int64_t>(c) * ldx, x[u]);
+      for (int q = 0; q < 4; ++q) {
+        col[q] = c[q];
+        val[q] = v[q];
       }
+    } else {
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int first = j + u * EPI;
-        if (first < cnt) {
-          const int avail = cnt - first < EPI ? cnt - first : EPI;
-          int done = 0;
-          while (done < avail) {
-            while (krel == cur_end) {
-              flush_row();
-              next_row();
-            }
-            const int room = cur_end - krel;
-            const int take = avail - done < room ? avail - done : room;
-            if (g >= done && g < done + take) {
+      for (int q = 0; q < NLD; ++q) {
+        const bool ok = decltype(full)::value || beg + k + q < L;
+        col[q] = ok ? cp[k + q] : 0;
+        val[q] = ok ? vp[k + q] : 0.0f;
+      }
+    }
+  };
+  auto walk = [&](auto full) {
+    constexpr bool FULL = decltype(full)::value;
+    fetch(0, full);
+    for (int kb = 0; kb < run; kb += KB) {
+      if (!FULL && kb >= L) break;   // no group has entries left (uniform)
+      const int e = beg + kb;
+      const unsigned bits = (ends[e >> 5] >> (e & 31)) & ((1u << KB) - 1u);
+      RawVec<T, EPV> x[KB];
+      float v[KB];
+      const int src0 = g * LPR + (kb % HOLD) / NLD;
 #pragma unroll
-              for (int q = 0; q < EPV; ++q) acc[q] = __fmaf_rn(v[u], x[u][q], acc[q]);
-            }
-            done += take;
-            krel += take;
+      for (int u = 0; u < KB; ++u) {
+        const unsigned c = static_cast<unsigned>(__shfl(col[u % NLD], src0 + u / NLD, kWave));
+        v[u] = __shfl(val[u % NLD], src0 + u / NLD, kWave);
+        if (FULL || e + u < L) {
+          if (kAnyPitch) x[u].load(xs + c * ldx);
+          else x[u].load(reinterpret_cast<const T*>(reinterpret_cast<const char*>(xs) +
+                                                    static_cast<uint64_t>(c) * static_cast<uint32_t>(ldx * sizeof(T))));
+        }
+      }
+      if ((kb + KB) % HOLD == 0 && kb + KB < run) fetch(kb + KB, full);
+#pragma unroll
+      for (int u = 0; u < KB; ++u) {
+        if (FULL || e + u < L) x[u].fma_into(v[u], acc);
+        if (bits & (1u << u)) {
+          const int row = row_of[e + u];
+          if (open) {
+            first_row = row;
+#pragma unroll
+            for (int c = 0; c < EPV; ++c) first[c] = acc[c];
+          } else {
+            store_row(row, acc);
           }
+          open = false;   // every later row begins inside the run
+          ended = true;
+#pragma unroll
+          for (int c = 0; c < EPV; ++c) acc[c] = 0.0f;
         }
       }
     }
-  }
+  };
+  const bool began_open = open;
+  if (L == kChunk) walk(std::true_type{});
+  else walk(std::false_type{});
 
-  int tr = -1;
-  if (cur_end > L) {
-    float fin[FIN];
-    reduce_groups(fin);
-    if (head) {
-      store_partial(phead, fin);
-    } else {
-      store_partial(ptail, fin);
-      tr = r;
-    }
-  } else {
-    flush_row();
-    next_row();
-    float zero[FIN];
+  // ---- rows that cross runs: what is left open is carried over the groups, in group order ----
+  bool any = ended;   // a row ended in this group or in the scanned ones before it
 #pragma unroll
-    for (int c = 0; c < FIN; ++c) zero[c] = 0.0f;
-    while (r < n_rows && cur_end == L) {
-      store_y(r, zero);
-      next_row();
+  for (int d = LPR; d < 64; d <<= 1) {
+    float up[EPV];
+#pragma unroll
+    for (int c = 0; c < EPV; ++c) up[c] = __shfl_up(acc[c], d, kWave);
+    const bool up_any = __shfl_up(any ? 1 : 0, d, kWave) != 0;
+    if (lane >= d) {
+      if (!any) {
+#pragma unroll
+        for (int c = 0; c < EPV; ++c) acc[c] = up[c] + acc[c];
+      }
+      any = any || up_any;
     }
   }
-  if (lane == 0 && blockIdx.y == 0) tail_row[chunk] = tr;
+  // what the groups before this one left open
+  float carry[EPV];
+#pragma unroll
+  for (int c = 0; c < EPV; ++c) {
+    carry[c] = __shfl_up(acc[c], LPR % 64, kWave);
+    if (g == 0 || LPR == 64) carry[c] = 0.0f;
+  }
+  const int up_any = __shfl_up(any ? 1 : 0, LPR % 64, kWave);
+  const bool before = LPR < 64 && g > 0 && up_any != 0;
+  if (ended && began_open) {
+#pragma unroll
+    for (int c = 0; c < EPV; ++c) first[c] = carry[c] + first[c];
+    if (head && !before) store_piece(phead, first);
+    else store_row(first_row, first);
+  }
+  if (g == NG - 1) {
+    if (head && !any) store_piece(phead, acc);   // the whole chunk lies inside one row
+    else if (tr >= 0) store_piece(ptail, acc);
+  }
+  const bool none = __shfl(any ? 1 : 0, 63, kWave) == 0;
+  if (lane == 0 && blockIdx.y == 0) tail_row[chunk] = head && none ? -1 : tr;
 }
 
-// Adds the pieces of every row that straddles chunk borders, in chunk order.
+// Adds the pieces of every row that straddles chunk borders, in chunk order. grid.y cuts the columns, so that
+// the longest rows (hundreds of pieces, one after another) are summed by several wavefronts.
 template <typename T, int EPV>
 __global__ __launch_bounds__(kSpmmThreads) void spmm_fixup_kernel(
     const int64_t* __restrict__ rowptr, const int* __restrict__ tail_row, int64_t nchunks,
     const float* __restrict__ phead, const float* __restrict__ ptail, T* __restrict__ Y, T* __restrict__ Y2,
     int64_t ldy, int dim, int n_rows, int kChunk) {
+  constexpr int NF = EPV == 1 ? 1 : 4;   // floats per piece vector
+  constexpr int NV = EPV / NF;
+  constexpr int U = 8 / NV;              // pieces in flight
   const int lane = threadIdx.x & 63;
   const int64_t chunk = static_cast<int64_t>(blockIdx.x) * kSpmmWaves + (threadIdx.x >> 6);
   if (chunk >= nchunks) return;
   const int r = tail_row[chunk];
   if (r < 0 || r >= n_rows) return;
+  if ((static_cast<int>(blockIdx.y) * 64 + lane) * EPV >= dim) return;
+  const int col = min((static_cast<int>(blockIdx.y) * 64 + lane) * EPV, dim - EPV);
   // last chunk that starts inside row r: the one that holds the row's last entry (the row runs past
   // this chunk, so it has one). Computed, not walked: the longest rows span hundreds of chunks.
   const int64_t last = (rowptr[r + 1] - 1) / kChunk;
-  for (int col = lane * EPV; col < dim; col += 64 * EPV) {
-    float acc[EPV];
+  float acc[EPV];
+  RawVec<float, NF> t[U][NV];
+  auto load = [&](const float* buf, int64_t c, RawVec<float, NF> (&v)[NV]) {
 #pragma unroll
-    for (int c = 0; c < EPV; ++c) acc[c] = ptail[chunk * static_cast<int64_t>(dim) + col + c];
-    int64_t c2 = chunk + 1;
-    for (; c2 + 3 <= last; c2 += 4) {
-      float t[4][EPV];
+    for (int h = 0; h < NV; ++h) v[h].load(buf + c * static_cast<int64_t>(dim) + col + h * NF);
+  };
+  auto add = [&](const RawVec<float, NF> (&v)[NV]) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
+    for (int h = 0; h < NV; ++h) {
+      float a[NF];
 #pragma unroll
-        for (int c = 0; c < EPV; ++c) t[q][c] = phead[(c2 + q) * static_cast<int64_t>(dim) + col + c];
+      for (int c = 0; c < NF; ++c) a[c] = acc[h * NF + c];
+      v[h].fma_into(1.0f, a);
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int c = 0; c < EPV; ++c) acc[c] = acc[c] + t[q][c];
+      for (int c = 0; c < NF; ++c) acc[h * NF + c] = a[c];
     }
-    for (; c2 <= last; ++c2)
+  };
 #pragma unroll
-      for (int c = 0; c < EPV; ++c) acc[c] = acc[c] + phead[c2 * static_cast<int64_t>(dim) + col + c];
-    if (Y) VecIO<T, EPV>::store(Y + static_cast<int64_t>(r) * ldy + col, acc);
-    if (Y2) {
+  for (int c = 0; c < EPV; ++c) acc[c] = 0.0f;
+  load(ptail, chunk, t[0]);
+  add(t[0]);
+  int64_t c2 = chunk + 1;
+  for (; c2 + U - 1 <= last; c2 += U) {
 #pragma unroll
-      for (int c = 0; c < EPV; ++c) acc[c] = acc[c] > 0.0f ? acc[c] : 0.0f;
-      VecIO<T, EPV>::store(Y2 + static_cast<int64_t>(r) * ldy + col, acc);
-    }
+    for (int q = 0; q < U; ++q) load(phead, c2 + q, t[q]);
+#pragma unroll
+    for (int q = 0; q < U; ++q) add(t[q]);
+  }
+  for (; c2 <= last; ++c2) {
+    load(phead, c2, t[0]);
+    add(t[0]);
+  }
+  if (Y) RawVec<T, EPV>::store(Y + static_cast<int64_t>(r) * ldy + col, acc);
+  if (Y2) {
+#pragma unroll
+    for (int c = 0; c < EPV; ++c) acc[c] = acc[c] > 0.0f ? acc[c] : 0.0f;
+    RawVec<T, EPV>::store(Y2 + static_cast<int64_t>(r) * ldy + col, acc);
   }
 }
 
@@ -552,15 +633,43 @@ size_t spmm_workspace_bytes(int64_t nnz, int32_t dim) {
          2 * align_up(static_cast<size_t>(nc) * dim * sizeof(float), 256);
 }
 
+// Lanes per entry: a slice of the feature matrix is lpr lane-vectors (16 bytes each) wide.
+//  - Rows of whole 128-byte lines: slices of one line (8 lanes) keep the gathered table small, slices of two
+//    lines (16) halve what is spent per entry and slice. Two lines as long as such a slice of the matrix fits
+//    the 256 MB memory-side cache. Measured, 8 / 16 lanes at 256 floats a row: 68 k gathered rows (18 MB a
+//    slice) 97 / 89 us, 300 k (77 MB) 3.39 / 3.16 ms; 2.1 M (537 MB) 20.5 / 23.9 ms, 7.1 M (1.8 GB) 21.7 /
+//    23.0 ms; 476 k rows of 1024 bf16 (122 MB) 647 / 601 us.
+//  - Other rows of at most 32 vectors: one slice, the group just wide enough (rows start anywhere in a line,
+//    so every extra slice fetches a line twice: 100 floats, 32 / 16 / 8 lanes 2.97 / 3.54 / 4.66 ms).
+//  - Longer ones: 16 (602 floats, 8 / 16 / 32 lanes: 399 / 373 / 400 us).
+static int pick_lanes(int dim, int epv, int64_t n_cols) {
+  const int nvec = static_cast<int>(ceil_div(dim, epv));
+  int lpr = 2;
+  if (nvec > 8 && dim % (8 * epv) == 0) return nvec % 16 == 0 && n_cols * 256 <= (int64_t(256) << 20) ? 16 : 8;
+  if (nvec > 32) return 16;
+  while (lpr < nvec) lpr <<= 1;
+  return lpr;
+}
+
 template <typename T, int EPV>
 static int launch_spmm(const cdf_csr* A, const T* X, int64_t ldx, T* Y, T* Y2, int64_t ldy, int dim, void* ws,
                        hipStream_t st) {
-  const int chunk = pick_chunk(A->nnz);
-  const int64_t nc = spmm_chunks(A->nnz);
+  const int plan_chunk = pick_chunk(A->nnz);
+  const int64_t plan_chunks = spmm_chunks(A->nnz);
+  const int nvec = static_cast<int>(ceil_div(dim, EPV));
+  const int lpr = EPV == 1 ? 8 : pick_lanes(dim, EPV, A->n_cols);
+  const int slices = static_cast<int>(ceil_div(nvec, lpr));
+  // the plan's chunks, several at a time where the lane groups are many: a run has at least one block of entries
+  int chunk = plan_chunk, step = 1;
+  while (chunk < kWalkBlock * (64 / lpr)) {
+    chunk *= 2;
+    step *= 2;
+  }
+  const int64_t nc = A->nnz <= 0 ? 1 : ceil_div(A->nnz, chunk);
   char* w = static_cast<char*>(ws);
   int* own_chunk_row = reinterpret_cast<int*>(w);
-  int* tail_row = own_chunk_row + nc;
-  w += align_up(static_cast<size_t>(nc) * 2 * sizeof(int), 256);
+  int* tail_row = own_chunk_row + plan_chunks;
+  w += align_up(static_cast<size_t>(plan_chunks) * 2 * sizeof(int), 256);
   float* phead = reinterpret_cast<float*>(w);
   w += align_up(static_cast<size_t>(nc) * dim * sizeof(float), 256);
   float* ptail = reinterpret_cast<float*>(w);
@@ -571,71 +680,41 @@ static int launch_spmm(const cdf_csr* A, const T* X, int64_t ldx, T* Y, T* Y2, i
     {
       ProfScope ps(K_SPMM_PLAN, st);
       chunk_rows_kernel<<<static_cast<unsigned>(ceil_div(A->n_rows, 256)), 256, 0, st>>>(A->rowptr, A->n_rows,
-                                                                                         own_chunk_row, chunk);
+                                                                                         own_chunk_row, plan_chunk);
     }
     CDF_LAUNCH_CHECK("cdf_spmm/chunk_rows");
     chunk_row = own_chunk_row;
   }
   const unsigned nblocks = static_cast<unsigned>(ceil_div(nc, kSpmmWaves));
-  const int per_pass = 64 * EPV;
-  const int np = static_cast<int>(ceil_div(dim, per_pass));
-  const int nvec = dim / EPV;
-  constexpr bool lane16 = EPV * static_cast<int>(sizeof(T)) == 16;   // 16-byte lane vectors
-#define CDF_SPMM_ARGS                                                                                      \
-  (A->rowptr, A->colidx, A->vals, A->n_rows, A->nnz, X, ldx, Y, Y2, ldy, dim, chunk_row, nc, phead, ptail, \
-   tail_row, chunk)
-#define CDF_SPMM_ARGS_X                                                                                    \
-  (A->rowptr, A->colidx, A->vals, A->n_rows, A->nnz, X, ldx, Y, Y2, ldy, dim, chunk_row, nc, phead, ptail, \
-   tail_row, chunk, XformArgs{})
-  // Lanes per entry. Rows of whole 128-byte lines with eight or more entries on average: one line per
-  // row and slice (8 lanes of 16 bytes); it pays when the per-row, per-slice reduction and store are
-  // amortised. Rows of at most 32 lane-vectors: one slice, the lane group just wide enough for the row.
-  // Everything else: the whole wavefront per entry.
-  constexpr int min_avg = 8;
-  int lpr = 0, slices = 1;
-  if (lane16 && dim % (8 * EPV) == 0 && A->nnz >= static_cast<int64_t>(min_avg) * A->n_rows) {
-    lpr = 8;
-    slices = dim / (8 * EPV);
-  } else if (lane16 && nvec <= 32) {
-    lpr = 2;
-    while (lpr < nvec) lpr <<= 1;
-  }
-  if (lpr > 0) {
-    if constexpr (lane16) {
-      const dim3 grid(nblocks, static_cast<unsigned>(slices));
-      prof_begin(K_SPMM_SLICED, st);
-      // gather instructions in flight per wavefront: long rows (the forward matrix of a power-law
-      // partition averages ~70 entries) run 2-3 % faster with eight, short rows (its transpose, ~20)
-      // with four - measured both ways
-      const bool deep = A->nnz >= static_cast<int64_t>(40) * A->n_rows;
-      switch (lpr) {
-        case 2: spmm_sliced_kernel<T, EPV, 2, 4><<<grid, kSpmmThreads, 0, st>>> CDF_SPMM_ARGS; break;
-        case 4: spmm_sliced_kernel<T, EPV, 4, 4><<<grid, kSpmmThreads, 0, st>>> CDF_SPMM_ARGS; break;
-        case 8:
-          if (deep) spmm_sliced_kernel<T, EPV, 8, 8><<<grid, kSpmmThreads, 0, st>>> CDF_SPMM_ARGS;
-          else spmm_sliced_kernel<T, EPV, 8, 4><<<grid, kSpmmThreads, 0, st>>> CDF_SPMM_ARGS;
-          break;
-        case 16: spmm_sliced_kernel<T, EPV, 16, 4><<<grid, kSpmmThreads, 0, st>>> CDF_SPMM_ARGS; break;
-        default: spmm_sliced_kernel<T, EPV, 32, 4><<<grid, kSpmmThreads, 0, st>>> CDF_SPMM_ARGS; break;
-      }
-      prof_end(K_SPMM_SLICED, st);
-      CDF_LAUNCH_CHECK("cdf_spmm/sliced");
-    }
+  const dim3 grid(nblocks, static_cast<unsigned>(slices));
+  const size_t lds = static_cast<size_t>(kSpmmWaves) * walk_lds_ints(chunk) * sizeof(int);
+#define CDF_SPMM_ARGS                                                                                            \
+  (A->rowptr, A->colidx, A->vals, A->n_rows, A->nnz, X, static_cast<uint64_t>(ldx), Y, Y2, ldy, dim, chunk_row, step, \
+   nc, phead, ptail, tail_row, chunk)
+  prof_begin(K_SPMM_WALK, st);
+#define CDF_WALK(LPRV)                                                                             \
+  if (chunk >= 256) spmm_walk_kernel<T, EPV, LPRV, true><<<grid, kSpmmThreads, lds, st>>> CDF_SPMM_ARGS; \
+  else spmm_walk_kernel<T, EPV, LPRV, false><<<grid, kSpmmThreads, lds, st>>> CDF_SPMM_ARGS
+  if constexpr (EPV == 1) {
+    CDF_WALK(8);
   } else {
-    prof_begin(K_SPMM, st);
-    if (np <= 1) spmm_kernel<T, EPV, 1><<<nblocks, kSpmmThreads, 0, st>>> CDF_SPMM_ARGS_X;
-    else if (np <= 2) spmm_kernel<T, EPV, 2><<<nblocks, kSpmmThreads, 0, st>>> CDF_SPMM_ARGS_X;
-    else if (np <= 4) spmm_kernel<T, EPV, 4><<<nblocks, kSpmmThreads, 0, st>>> CDF_SPMM_ARGS_X;
-    else spmm_kernel<T, EPV, 8><<<nblocks, kSpmmThreads, 0, st>>> CDF_SPMM_ARGS_X;
-    prof_end(K_SPMM, st);
-    CDF_LAUNCH_CHECK("cdf_spmm/main");
+    switch (lpr) {
+      case 2: CDF_WALK(2); break;
+      case 4: CDF_WALK(4); break;
+      case 8: CDF_WALK(8); break;
+      case 16: CDF_WALK(16); break;
+      default: CDF_WALK(32); break;
+    }
   }
+#undef CDF_WALK
+  prof_end(K_SPMM_WALK, st);
 #undef CDF_SPMM_ARGS
-#undef CDF_SPMM_ARGS_X
+  CDF_LAUNCH_CHECK("cdf_spmm/walk");
   {
     ProfScope ps(K_SPMM_FIXUP, st);
-    spmm_fixup_kernel<T, EPV><<<nblocks, kSpmmThreads, 0, st>>>(A->rowptr, tail_row, nc, phead, ptail, Y, Y2, ldy, dim,
-                                                                 A->n_rows, chunk);
+    const dim3 fgrid(nblocks, static_cast<unsigned>(ceil_div(nvec, 64)));
+    spmm_fixup_kernel<T, EPV><<<fgrid, kSpmmThreads, 0, st>>>(A->rowptr, tail_row, nc, phead, ptail, Y, Y2, ldy, dim,
+                                                              A->n_rows, chunk);
   }
   CDF_LAUNCH_CHECK("cdf_spmm/fixup");
   return CDF_OK;
@@ -658,31 +737,24 @@ int spmm_run(const char* fn, const cdf_csr* A, const void* X, int64_t ldx, void*
   if (!ws || !aligned(ws, 256) || ws_bytes < spmm_workspace_bytes(A->nnz, dim))
     CDF_FAIL(CDF_ERR_WORKSPACE, "%s: workspace too small or unaligned (%zu < %zu)", fn, ws_bytes,
              spmm_workspace_bytes(A->nnz, dim));
-  // widest lane-vector that both operands allow; at most 8 passes of 64 lanes per launch
-  int epv = dt == CDF_BF16 ? 8 : 4;
-  for (; epv > 1; epv >>= 1) {
-    const size_t vb = esz * epv;
-    if (dim % epv == 0 && ldx % epv == 0 && ldy % epv == 0 && aligned(X, vb) && aligned(Y, vb) && aligned(Y2, vb)) break;
-  }
-  const int max_cols = 64 * epv * 8;
-  for (int col0 = 0; col0 < dim; col0 += max_cols) {
-    const int d = dim - col0 < max_cols ? dim - col0 : max_cols;
+  // 16-byte lane vectors at any alignment; rows narrower than one (and pitches of 4 GiB and more) go element-wise
+  const int full = dt == CDF_BF16 ? 8 : 4;
+  const bool vec = dim >= full && static_cast<uint64_t>(ldx) * esz <= 0xffffffffu && static_cast<uint64_t>(ldy) * esz <= 0xffffffffu;
+  constexpr int kMaxCols = 1 << 18;   // per launch (grid.y)
+  for (int col0 = 0; col0 < dim; col0 += kMaxCols) {
+    const int d = dim - col0 < kMaxCols ? dim - col0 : kMaxCols;
+    const bool v = vec && d >= full;
     int rc;
     if (dt == CDF_F32) {
       const float* x = static_cast<const float*>(X) + col0;
       float* y = Y ? static_cast<float*>(Y) + col0 : nullptr;
       float* y2 = Y2 ? static_cast<float*>(Y2) + col0 : nullptr;
-      rc = epv == 4 ? launch_spmm<float, 4>(A, x, ldx, y, y2, ldy, d, ws, st)
-           : epv == 2 ? launch_spmm<float, 2>(A, x, ldx, y, y2, ldy, d, ws, st)
-                      : launch_spmm<float, 1>(A, x, ldx, y, y2, ldy, d, ws, st);
+      rc = v ? launch_spmm<float, 4>(A, x, ldx, y, y2, ldy, d, ws, st) : launch_spmm<float, 1>(A, x, ldx, y, y2, ldy, d, ws, st);
     } else {
       const bf16_t* x = static_cast<const bf16_t*>(X) + col0;
       bf16_t* y = Y ? static_cast<bf16_t*>(Y) + col0 : nullptr;
       bf16_t* y2 = Y2 ? static_cast<bf16_t*>(Y2) + col0 : nullptr;
-      rc = epv == 8   ? launch_spmm<bf16_t, 8>(A, x, ldx, y, y2, ldy, d, ws, st)
-           : epv == 4 ? launch_spmm<bf16_t, 4>(A, x, ldx, y, y2, ldy, d, ws, st)
-           : epv == 2 ? launch_spmm<bf16_t, 2>(A, x, ldx, y, y2, ldy, d, ws, st)
-                      : launch_spmm<bf16_t, 1>(A, x, ldx, y, y2, ldy, d, ws, st);
+      rc = v ? launch_spmm<bf16_t, 8>(A, x, ldx, y, y2, ldy, d, ws, st) : launch_spmm<bf16_t, 1>(A, x, ldx, y, y2, ldy, d, ws, st);
     }
     if (rc != CDF_OK) return rc;
   }
@@ -736,14 +808,13 @@ int spmm_transform_run(const char* fn, const cdf_csr* A, const float* X, int64_t
   const size_t lds_main = (static_cast<size_t>(xf_row_floats(dim * g)) + kSpmmWaves * xf_row_floats(dim)) * sizeof(float);
   const size_t lds_fix = static_cast<size_t>(kSpmmWaves) * xf_row_floats(dim) * sizeof(float);
   const int np = static_cast<int>(ceil_div(dim, 256));
-  float* none = nullptr;
 #define CDF_XF_ARGS                                                                                              \
-  (A->rowptr, A->colidx, A->vals, A->n_rows, A->nnz, X, ldx, M, none, ldm, dim, chunk_row, nc, phead, ptail, tail_row, \
+  (A->rowptr, A->colidx, A->vals, A->n_rows, A->nnz, X, ldx, M, ldm, dim, chunk_row, nc, phead, ptail, tail_row, \
    chunk, xf)
   prof_begin(K_SPMM_XFORM, st);
-  if (np <= 1) spmm_kernel<float, 4, 1, true><<<nblocks, kSpmmThreads, lds_main, st>>> CDF_XF_ARGS;
-  else if (np <= 2) spmm_kernel<float, 4, 2, true><<<nblocks, kSpmmThreads, lds_main, st>>> CDF_XF_ARGS;
-  else spmm_kernel<float, 4, 4, true><<<nblocks, kSpmmThreads, lds_main, st>>> CDF_XF_ARGS;
+  if (np <= 1) spmm_transform_kernel<float, 4, 1><<<nblocks, kSpmmThreads, lds_main, st>>> CDF_XF_ARGS;
+  else if (np <= 2) spmm_transform_kernel<float, 4, 2><<<nblocks, kSpmmThreads, lds_main, st>>> CDF_XF_ARGS;
+  else spmm_transform_kernel<float, 4, 4><<<nblocks, kSpmmThreads, lds_main, st>>> CDF_XF_ARGS;
   prof_end(K_SPMM_XFORM, st);
 #undef CDF_XF_ARGS
   CDF_LAUNCH_CHECK("spmm + transform/main");

@@ -151,7 +151,7 @@ def summarise(workload, order, d, out_dir):
         c[0] += f
         c[1] += w
     for k in F:
-        if base(k) in ("spmm_kernel", "spmm_sliced_kernel"):
+        if base(k) == "spmm_walk_kernel":
             v = [x * 1024 * fs / 1e9 for x in F[k]["FETCH_SIZE"]]
             L.append("\n`%s` fetch GB of its first launches, in launch order: %s" % (k, ", ".join("%.2f" % x for x in v[:6])))
 

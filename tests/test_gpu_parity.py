@@ -410,6 +410,42 @@ def test_spmm_padded_pitch_long_rows(cdf, oracle):
         assert_rows_close(to_np(Y.contiguous()), want, what=f"Y dim {dim}")
 
 
+# every width class of the aggregation (lane groups of 2 ... 32 lanes, one and several slices, rows that are no
+# whole number of lane vectors, rows narrower than one) on a matrix of small chunks and on one of 256-entry chunks,
+# rows ending on and next to the borders of a lane group's run, from base addresses and pitches that are aligned to
+# an element only
+@pytest.mark.parametrize("dim", [1, 3, 4, 5, 7, 9, 17, 33, 41, 64, 100, 129, 256])
+@pytest.mark.parametrize("nnz_target", [20_000, 1_060_000])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_spmm_run_borders_and_element_aligned_rows(cdf, oracle, dim, nnz_target, dtype):
+    rs = np.random.default_rng(dim + nnz_target)
+    pattern = [8, 8, 16, 0, 32, 0, 0, 64, 128, 256, 7, 1, 9, 23, 33, 63, 65, 1, 127, 0, 385, 1025, 2, 0]
+    lens = np.array(pattern * (nnz_target // sum(pattern)) + [0, 0], np.int64)
+    rowptr = np.zeros(lens.size + 1, np.int64)
+    rowptr[1:] = np.cumsum(lens)
+    nnz, n_cols = int(rowptr[-1]), 3000
+    colidx = rs.integers(0, n_cols, nnz).astype(np.int32)
+    vals = rs.standard_normal(nnz).astype(np.float32)
+    X = torch.from_numpy(rs.standard_normal((n_cols, dim)).astype(np.float32)).to(dtype)
+    A = cdf.DeviceCsr(lens.size, n_cols, torch.from_numpy(rowptr), torch.from_numpy(colidx), torch.from_numpy(vals), DEV)
+    ws = ws_for(cdf, max(lens.size, n_cols), dim, nnz)
+    ldx, ldy = dim + 3, dim + 1
+    Xp = torch.full((n_cols * ldx + 1,), float("nan"), dtype=dtype, device=DEV)
+    Yp = torch.full((lens.size * ldy + 1,), 3.0, dtype=dtype, device=DEV)
+    xv, yv = Xp[1:].view(n_cols, ldx), Yp[1:].view(lens.size, ldy)
+    xv[:, :dim] = X.to(DEV)
+    cdf.cdf_spmm_fwd(A.struct, xv[:, :dim], yv[:, :dim], ws)
+    torch.cuda.synchronize()
+    # every term passes through at most 128 additions of a run, 16 of runs and pieces: |error| <= 160 * 2^-24 * the
+    # sum of the terms' magnitudes; a bf16 result adds half a step on either side
+    want = as_f64(oracle.spmm(rowptr, colidx, vals, n_cols, to_np(X)))
+    size = as_f64(oracle.spmm(rowptr, colidx, np.abs(vals), n_cols, to_np(X.abs())))
+    err = np.abs(as_f64(to_np(yv[:, :dim].contiguous())) - want)
+    step = 0.0 if dtype == torch.float32 else 2.0 ** -7
+    assert (err <= 160 * 2.0 ** -24 * (1 + step) * size + step * np.abs(want)).all(), float(err.max())
+    assert bool((yv[:, dim:] == 3.0).all()) and float(Yp[0]) == 3.0      # nothing outside the rows is written
+
+
 @pytest.mark.parametrize("f_in,f_out", [(128, 16), (16, 8), (256, 41), (256, 47), (100, 47), (512, 24), (1024, 12),
                                         (64, 64), (4, 1), (256, 64), (128, 70), (37, 8)])
 @pytest.mark.parametrize("relu", [True, False])
