@@ -18,6 +18,16 @@ int test_and_encode(const void* cur, void* cached, int32_t n_rows, int32_t dim, 
                     int32_t* n_sent, uint8_t* codes, float* meta, void* ws, size_t ws_bytes, void* stream);
 int spmm_run(const char* fn, const cdf_csr* A, const void* X, int64_t ldx, void* Y, void* Y2, int64_t ldy,
              int32_t dim, cdf_dtype dt, void* ws, size_t ws_bytes, hipStream_t st);
+int spmm_ordered_run(const char* fn, const cdf_csr* A, const void* X, int64_t ldx, void* Y, int64_t ldy, int32_t dim,
+                     cdf_dtype dt, void* ws, size_t ws_bytes, hipStream_t st);
+int dense_bwd_ws(const void* M, int64_t ldm, cdf_dtype dt, const float* W, const float* Zs, const float* dH, int32_t n,
+                 int32_t f_in, int32_t f_out, int relu, float* dW, void* dM, int64_t lddm, bool ordered_dm, void* ws,
+                 size_t ws_bytes, void* stream);
+
+// Backward steps whose committed cache depends on the codes keep the order of summation (see cdf_ordered.hip).
+static bool ordered_gradients(cdf_commit commit, cdf_qscheme qs, int32_t n_halo) {
+  return commit == CDF_COMMIT_DEQ && qs != CDF_Q_NONE && n_halo > 0;
+}
 
 // dZ = dH where Zs > 0, else 0 (16 bytes per lane; count is a multiple of 4 or the tail is scalar)
 __global__ __launch_bounds__(256) void relu_mask_kernel(const float* __restrict__ dH, const float* __restrict__ Zs,
@@ -50,7 +60,7 @@ static const char* const kKernelNames[K_COUNT] = {
     "filter_kernel", "scan_kernel", "compact_kernel", "quantize_kernel", "dequantize_kernel",
     "chunk_rows_kernel", "spmm_fixup_kernel", "gemm_kernel<FWD>", "gemm_kernel<DW>",
     "reduce_slabs_kernel", "gemm_kernel<DM>", "spmm_walk_kernel", "relu_mask_kernel", "test_encode_kernel",
-    "gather_codes_kernel", "spmm_transform_kernel"};
+    "gather_codes_kernel", "spmm_transform_kernel", "ordered_spmm_kernel"};
 constexpr int kProfCap = 8192;
 struct ProfRec {
   int id;
@@ -209,10 +219,14 @@ extern "C" int cdf_gcn_layer_bwd(const cdf_layer_bwd_args* p, void* ws, size_t w
     CDF_FAIL(CDF_ERR_WORKSPACE, "cdf_gcn_layer_bwd: workspace too small or unaligned (%zu < %zu)", ws_bytes, need);
   char* w = static_cast<char*>(ws);
   const size_t esz = elem_bytes(p->dt);
-  int rc = cdf_dense_bwd(p->M, p->f_in, p->dt, p->W, p->Zs, p->dH, p->n_loc, p->f_in, p->f_out, p->relu, p->dW,
-                         p->need_dx ? p->dM : nullptr, p->f_in, w + fw, ws_bytes - fw, stream);
+  const bool ordered = ordered_gradients(p->commit, p->qs, p->n_halo);
+  int rc = dense_bwd_ws(p->M, p->f_in, p->dt, p->W, p->Zs, p->dH, p->n_loc, p->f_in, p->f_out, p->relu, p->dW,
+                        p->need_dx ? p->dM : nullptr, p->f_in, ordered, w + fw, ws_bytes - fw, stream);
   if (rc != CDF_OK || !p->need_dx) return rc;
-  rc = cdf_spmm_bwd(p->At, p->dM, p->f_in, p->dxfull, p->f_in, p->f_in, p->dt, w + fw, ws_bytes - fw, stream);
+  if (ordered)
+    rc = spmm_ordered_run("cdf_gcn_layer_bwd", p->At, p->dM, p->f_in, p->dxfull, p->f_in, p->f_in, p->dt, w + fw,
+                          ws_bytes - fw, static_cast<hipStream_t>(stream));
+  else rc = cdf_spmm_bwd(p->At, p->dM, p->f_in, p->dxfull, p->f_in, p->f_in, p->dt, w + fw, ws_bytes - fw, stream);
   if (rc != CDF_OK) return rc;
   if (p->n_halo > 0) {
     CDF_REQUIRE(p->gcache_sent && p->mask && p->idx && p->n_sent && p->codes && p->meta,
@@ -297,7 +311,11 @@ extern "C" int cdf_gcn_layer_tf_bwd(const cdf_layer_tf_bwd_args* p, void* ws, si
     CDF_LAUNCH_CHECK("cdf_gcn_layer_tf_bwd/mask");
     dz = p->dZ;
   }
-  int rc = cdf_spmm_bwd(p->At, dz, p->f_out, p->dtfull, p->f_out, p->f_out, CDF_F32, w + fw, ws_bytes - fw, stream);
+  int rc;
+  if (ordered_gradients(p->commit, p->qs, p->n_halo))
+    rc = spmm_ordered_run("cdf_gcn_layer_tf_bwd", p->At, dz, p->f_out, p->dtfull, p->f_out, p->f_out, CDF_F32, w + fw,
+                          ws_bytes - fw, st);
+  else rc = cdf_spmm_bwd(p->At, dz, p->f_out, p->dtfull, p->f_out, p->f_out, CDF_F32, w + fw, ws_bytes - fw, stream);
   if (rc != CDF_OK) return rc;
   if (p->n_halo > 0) {
     CDF_REQUIRE(p->gcache_sent && p->mask && p->idx && p->n_sent && p->codes && p->meta,

@@ -261,8 +261,11 @@ struct RawVec<float, 4> {
 #pragma unroll
     for (int c = 0; c < 4; ++c) acc[c] = __fmaf_rn(w, v[c], acc[c]);
   }
+  template <bool STREAM = false>
   static __device__ __forceinline__ void store(float* p, const float (&a)[4]) {
-    *reinterpret_cast<v_t*>(p) = v_t{a[0], a[1], a[2], a[3]};
+    const v_t t = {a[0], a[1], a[2], a[3]};
+    if (STREAM) __builtin_nontemporal_store(t, reinterpret_cast<v_t*>(p));
+    else *reinterpret_cast<v_t*>(p) = t;
   }
 };
 template <>
@@ -277,11 +280,13 @@ struct RawVec<bf16_t, 8> {
       acc[2 * c + 1] = __fmaf_rn(w, __uint_as_float(v[c] & 0xffff0000u), acc[2 * c + 1]);
     }
   }
+  template <bool STREAM = false>
   static __device__ __forceinline__ void store(bf16_t* p, const float (&a)[8]) {
     v_t t;
 #pragma unroll
     for (int c = 0; c < 4; ++c) t[c] = f2bf(a[2 * c]) | (static_cast<uint32_t>(f2bf(a[2 * c + 1])) << 16);
-    *reinterpret_cast<v_t*>(p) = t;
+    if (STREAM) __builtin_nontemporal_store(t, reinterpret_cast<v_t*>(p));
+    else *reinterpret_cast<v_t*>(p) = t;
   }
 };
 template <typename T>
@@ -293,6 +298,7 @@ struct RawVec<T, 1> {
     VecIO<T, 1>::load(&v, x);
     acc[0] = __fmaf_rn(w, x[0], acc[0]);
   }
+  template <bool STREAM = false>
   static __device__ __forceinline__ void store(T* p, const float (&a)[1]) { VecIO<T, 1>::store(p, a); }
 };
 
@@ -306,7 +312,7 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_walk_kernel(
     const int64_t* __restrict__ rowptr, const int* __restrict__ colidx, const float* __restrict__ vals,
     int n_rows, int64_t nnz, const T* __restrict__ X, uint64_t ldx, T* __restrict__ Y, T* __restrict__ Y2,
     int64_t ldy, int dim, const int* __restrict__ chunk_row, int plan_step, int64_t nchunks, float* __restrict__ phead,
-    float* __restrict__ ptail, int* __restrict__ tail_row, int kChunk) {
+    float* __restrict__ ptail, int* __restrict__ tail_row, int kChunk, int stream_csr) {
   constexpr int NG = 64 / LPR;
   constexpr int KB = kWalkBlock;
   // (column, value) pairs a lane fetches at a time, and entries of its run that its group then holds
@@ -329,12 +335,13 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_walk_kernel(
   auto store_row = [&](int row, const float (&a)[EPV]) {
     const uint64_t at = (kAnyPitch ? static_cast<uint64_t>(row) * static_cast<uint64_t>(ldy)
                                    : static_cast<uint64_t>(static_cast<uint32_t>(row)) * static_cast<uint32_t>(ldy)) + col0;
-    if (Y) RawVec<T, EPV>::store(Y + at, a);
+    // finished rows are not read again here: streamed past the caches that hold the gathered rows
+    if (Y) RawVec<T, EPV>::template store<true>(Y + at, a);
     if (Y2) {
       float pos[EPV];
 #pragma unroll
       for (int c = 0; c < EPV; ++c) pos[c] = a[c] > 0.0f ? a[c] : 0.0f;
-      RawVec<T, EPV>::store(Y2 + at, pos);
+      RawVec<T, EPV>::template store<true>(Y2 + at, pos);
     }
   };
   auto store_piece = [&](float* buf, const float (&a)[EPV]) {
@@ -414,8 +421,15 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_walk_kernel(
     if constexpr (decltype(full)::value && NLD == 4) {
       typedef int i4u __attribute__((ext_vector_type(4), aligned(4)));
       typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
-      const i4u c = *reinterpret_cast<const i4u*>(cp + k);
-      const f4u v = *reinterpret_cast<const f4u*>(vp + k);
+      i4u c;
+      f4u v;
+      if (stream_csr) {
+        c = __builtin_nontemporal_load(reinterpret_cast<const i4u*>(cp + k));
+        v = __builtin_nontemporal_load(reinterpret_cast<const f4u*>(vp + k));
+      } else {
+        c = *reinterpret_cast<const i4u*>(cp + k);
+        v = *reinterpret_cast<const f4u*>(vp + k);
+      }
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         col[q] = c[q];
@@ -577,7 +591,7 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_fixup_kernel(
 // Entries per wavefront: 64 or 128 on small matrices (so that even a few thousand entries spread over
 // all compute units and a wavefront's serial walk stays short), 256 from 1 M entries, up to 1024 for
 // large ones (fewer straddling-row pieces). Always a multiple of 64; a function of nnz alone.
-static int pick_chunk(int64_t nnz) {
+int spmm_chunk(int64_t nnz) {
   int c = 64;
   while (c < kChunk && nnz / (2 * c) >= 4096) c *= 2;
   while (c >= kChunk && c < 1024 && nnz / (2 * c) >= 65536) c *= 2;
@@ -616,7 +630,7 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_fixup_transform_kernel(
   transform_row(rb, xf.W, dim, xf, r, lane);
 }
 
-int64_t spmm_chunks(int64_t nnz) { return nnz <= 0 ? 1 : ceil_div(nnz, pick_chunk(nnz)); }
+int64_t spmm_chunks(int64_t nnz) { return nnz <= 0 ? 1 : ceil_div(nnz, spmm_chunk(nnz)); }
 
 // Upper bound of spmm_chunks over every matrix of at most nnz entries (the chunk size steps up with nnz,
 // so the count itself is not monotone).
@@ -654,7 +668,7 @@ static int pick_lanes(int dim, int epv, int64_t n_cols) {
 template <typename T, int EPV>
 static int launch_spmm(const cdf_csr* A, const T* X, int64_t ldx, T* Y, T* Y2, int64_t ldy, int dim, void* ws,
                        hipStream_t st) {
-  const int plan_chunk = pick_chunk(A->nnz);
+  const int plan_chunk = spmm_chunk(A->nnz);
   const int64_t plan_chunks = spmm_chunks(A->nnz);
   const int nvec = static_cast<int>(ceil_div(dim, EPV));
   const int lpr = EPV == 1 ? 8 : pick_lanes(dim, EPV, A->n_cols);
@@ -687,10 +701,13 @@ static int launch_spmm(const cdf_csr* A, const T* X, int64_t ldx, T* Y, T* Y2, i
   }
   const unsigned nblocks = static_cast<unsigned>(ceil_div(nc, kSpmmWaves));
   const dim3 grid(nblocks, static_cast<unsigned>(slices));
+  // the CSR arrays are streamed past the caches where they exceed the memory-side cache and cannot be found
+  // there by the next slice (144 M entries: 21.6 -> 21.3 ms; 1.8 M entries: 90 -> 99 us, hence the line)
+  const int stream_csr = A->nnz * 8 > (int64_t(256) << 20) ? 1 : 0;
   const size_t lds = static_cast<size_t>(kSpmmWaves) * walk_lds_ints(chunk) * sizeof(int);
 #define CDF_SPMM_ARGS                                                                                            \
   (A->rowptr, A->colidx, A->vals, A->n_rows, A->nnz, X, static_cast<uint64_t>(ldx), Y, Y2, ldy, dim, chunk_row, step, \
-   nc, phead, ptail, tail_row, chunk)
+   nc, phead, ptail, tail_row, chunk, stream_csr)
   prof_begin(K_SPMM_WALK, st);
 #define CDF_WALK(LPRV)                                                                             \
   if (chunk >= 256) spmm_walk_kernel<T, EPV, LPRV, true><<<grid, kSpmmThreads, lds, st>>> CDF_SPMM_ARGS; \
@@ -784,7 +801,7 @@ int spmm_transform_run(const char* fn, const cdf_csr* A, const float* X, int64_t
   if (!ws || !aligned(ws, 256) || ws_bytes < spmm_workspace_bytes(A->nnz, dim))
     CDF_FAIL(CDF_ERR_WORKSPACE, "%s: workspace too small or unaligned (%zu < %zu)", fn, ws_bytes,
              spmm_workspace_bytes(A->nnz, dim));
-  const int chunk = pick_chunk(A->nnz);
+  const int chunk = spmm_chunk(A->nnz);
   const int64_t nc = spmm_chunks(A->nnz);
   char* w = static_cast<char*>(ws);
   int* own_chunk_row = reinterpret_cast<int*>(w);
@@ -872,7 +889,7 @@ extern "C" int cdf_spmm_plan(const cdf_csr* A, int32_t* plan, size_t plan_bytes,
   {
     ProfScope ps(K_SPMM_PLAN, st);
     chunk_rows_kernel<<<static_cast<unsigned>(ceil_div(A->n_rows, 256)), 256, 0, st>>>(A->rowptr, A->n_rows, plan,
-                                                                                       pick_chunk(A->nnz));
+                                                                                       spmm_chunk(A->nnz));
   }
   CDF_LAUNCH_CHECK("cdf_spmm_plan");
   return CDF_OK;

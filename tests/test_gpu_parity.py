@@ -550,6 +550,68 @@ def test_dense_fwd_bwd(cdf, oracle, n, f, g, relu, dtype):
         assert_bf16_close(to_np(dM), odM, "dM")
 
 
+# fp32 products from split bf16 operands: sizes around the tiles (64 and 128 rows, 64 and 128 columns, steps of 32),
+# widths with every alignment, and pitches above the width
+@pytest.mark.parametrize("n,f,g", [(1, 1, 1), (63, 33, 7), (64, 32, 64), (65, 31, 65), (129, 9, 129), (300, 602, 41),
+                                   (1000, 100, 47), (257, 8, 8), (40, 257, 300), (70000, 129, 130), (70000, 64, 200)])
+@pytest.mark.parametrize("relu", [True, False])
+def test_dense_fp32_split_error(cdf, n, f, g, relu):
+    """Every result within the bound of fp32 arithmetic: one rounding per accumulated term (2^-24 of the sum of the
+    terms' magnitudes times their number is an upper bound; the square root of it is what sums of this kind show,
+    and 8 times that is asked for) - against float64 on the same inputs."""
+    gen = torch.Generator(device=DEV).manual_seed(n * 7 + f + g)
+    Mp = torch.randn(n, f + 3, generator=gen, device=DEV)
+    M = Mp[:, :f]
+    W, dH, Zs = (torch.randn(*s, generator=gen, device=DEV) for s in ((f, g), (n, g), (n, g)))
+    H, dW, dMp = torch.empty(n, g, device=DEV), torch.empty(f, g, device=DEV), torch.full((n, f + 1), 5.0, device=DEV)
+    ws = ws_for(cdf, n, max(f, g))
+    cdf.cdf_dense_fwd(M, W, relu, None, H)
+    cdf.cdf_dense_bwd(M, W, Zs, dH, relu, dW, dMp[:, :f], ws)
+    torch.cuda.synchronize()
+    m, w, dz = M.double(), W.double(), torch.where(Zs > 0, dH, torch.zeros_like(dH)).double() if relu else dH.double()
+    for got, a, b, what in ((H, m, w, "H"), (dW, m.t().contiguous(), dz, "dW"), (dMp[:, :f], dz, w.t().contiguous(), "dM")):
+        want, size = a @ b, a.abs() @ b.abs()
+        if what == "H" and relu:
+            want = want.clamp(min=0)
+        bound = 8 * (a.shape[1] ** 0.5) * 2.0 ** -24 * size + 1e-37
+        assert bool(((got.double() - want).abs() <= bound).all()), (what, float(((got.double() - want).abs() / bound).max()))
+    assert bool((dMp[:, f] == 5.0).all())
+
+
+@pytest.mark.parametrize("n,f,g", [(200, 40, 70), (12, 5, 3), (700, 130, 140)])
+def test_dense_fp32_infinities_and_huge_values(cdf, n, f, g):
+    """Operands with infinities, NaN and values above the largest bf16: infinite and NaN results where fp32
+    arithmetic has them and nowhere else, the other results unharmed."""
+    rs = np.random.default_rng(n)
+    M, W, dH = (rs.standard_normal(s).astype(np.float32) for s in ((n, f), (f, g), (n, g)))
+    M[3, 2], M[5, 1], M[6, 4], M[n - 1, f - 1] = np.inf, -np.inf, np.nan, 3.4e38
+    W[:, 1] = 0.0
+    # the products of the huge finite values stay finite, whatever order they are added in
+    W[f - 1] *= 0.1
+    W[:, 0] *= 0.1
+    dH[n - 1] *= 0.01
+    M[4] *= 0.01
+    dH[2, 1], dH[4, 0], dH[n - 1, g - 1] = np.inf, 3.4e38, np.nan
+    t = lambda a: torch.from_numpy(a).to(DEV)
+    H, dW, dM = torch.empty(n, g, device=DEV), torch.empty(f, g, device=DEV), torch.empty(n, f, device=DEV)
+    ws = ws_for(cdf, n, max(f, g))
+    cdf.cdf_dense_fwd(t(M), t(W), False, H, None)
+    cdf.cdf_dense_bwd(t(M), t(W), None, t(dH), False, dW, dM, ws)
+    torch.cuda.synchronize()
+    with np.errstate(all="ignore"):
+        for got, a, b in ((H, M, W), (dW, M.T, dH), (dM, dH, W.T)):
+            got = to_np(got)
+            want = np.zeros((a.shape[0], b.shape[1]), np.float32)
+            for k in range(a.shape[1]):                       # one fp32 term after another
+                want = want + a[:, k:k + 1] * b[k:k + 1]
+            assert np.array_equal(np.isnan(got), np.isnan(want))
+            inf = np.isinf(want)
+            assert np.array_equal(got[inf], want[inf]) and np.array_equal(np.isinf(got), inf)
+            fin = np.isfinite(want)
+            size = np.nan_to_num(np.abs(a.astype(np.float64)), nan=0, posinf=0) @ np.nan_to_num(np.abs(b.astype(np.float64)), nan=0, posinf=0)
+            assert (np.abs(got[fin].astype(np.float64) - want[fin]) <= 4 * a.shape[1] * 2.0 ** -24 * size[fin]).all()
+
+
 @pytest.mark.parametrize("n,f,g", [(131072 + 77, 256, 192), (131072, 128, 128)])
 def test_dense_bf16_many_row_tiles(cdf, oracle, n, f, g):
     """bf16 activations, more than a thousand row tiles: the 1-D grids of the forward and dM products
@@ -862,6 +924,39 @@ def test_tf_layer_mid_shrunk(cdf, oracle):
 def test_tf_layer_large_shrunk(cdf, oracle):
     P = configs.build_partition(configs.shrink(configs.LARGE, 20000))
     tf_layer_case(cdf, oracle, P, 256, 64, 0.05, 8, 0, 1, True, epochs=2)
+
+
+@pytest.mark.parametrize("f_in,f_out,dtype", [(16, 8, torch.float32), (41, 30, torch.float32), (100, 47, torch.float32),
+                                              (602, 33, torch.float32), (256, 64, torch.float32), (128, 20, torch.bfloat16)])
+def test_backward_with_recovered_commit_keeps_its_order_of_summation(cdf, f_in, f_out, dtype):
+    """COMMIT_DEQ steps take the kernels that keep the order of summation, the others do not; the gradients of the
+    two differ by roundings only (dM: at most f_out terms, dxfull: the longest row's, 2^-24 each; bf16: one step)."""
+    P = configs.build_partition(configs.TINY)
+    A = cdf.DeviceCsr(P.n_loc, P.n_loc + P.n_halo, P.rowptr, P.colidx, P.vals, DEV)
+    At = cdf.DeviceCsr(P.n_loc + P.n_halo, P.n_loc, P.t_rowptr, P.t_colidx, P.t_vals, DEV)
+    got = {}
+    for commit in (cdf.COMMIT_CUR, cdf.COMMIT_DEQ):
+        L = cdf.LayerBuffers(A, At, P.n_loc, P.n_halo, f_in, f_out, dtype=dtype, device=DEV)
+        gen = torch.Generator(device=DEV).manual_seed(9)
+        L.M.copy_(torch.randn(P.n_loc, f_in, generator=gen, device=DEV))
+        L.W.copy_(torch.randn(f_in, f_out, generator=gen, device=DEV))
+        L.dH.copy_(torch.randn(P.n_loc, f_out, generator=gen, device=DEV))
+        L.Z.copy_(torch.randn(P.n_loc, f_out, generator=gen, device=DEV))
+        ws = torch.zeros(L.workspace_bytes(), dtype=torch.uint8, device=DEV)
+        cdf.cdf_profile_enable(True)
+        cdf.cdf_gcn_layer_bwd(L.bwd_args(0.05, commit=commit), ws)
+        torch.cuda.synchronize()
+        names = {n for n, _ in cdf.cdf_profile_read_all()}
+        cdf.cdf_profile_enable(False)
+        assert ("ordered_spmm_kernel" in names) == (commit == cdf.COMMIT_DEQ)
+        assert ("spmm_walk_kernel" in names) == (commit != cdf.COMMIT_DEQ)
+        got[commit] = (L.dM.double(), L.dxfull.double(), L.dW.clone())
+    a, b = got[cdf.COMMIT_CUR], got[cdf.COMMIT_DEQ]
+    assert torch.equal(a[2], b[2])
+    step = 2.0 ** -7 if dtype == torch.bfloat16 else 0.0
+    for x, y in zip(a[:2], b[:2]):
+        scale = y.abs().amax(1, keepdim=True).clamp(min=1e-30)
+        assert bool(((x - y).abs() <= 512 * 2.0 ** -24 * scale + 2 * step * scale).all())
 
 
 @pytest.mark.parametrize("n,classes", [(1000, 8), (777, 41), (300, 64), (130, 47), (64, 1), (500, 200)])
