@@ -268,7 +268,7 @@ def kernel_rooflines(model, w, kernels):
         # one-pass test + message build: every row read once, sent rows committed and coded
         "test_encode_kernel": avg([h * (2 * f * esz + 1) + sn[i] * (f * esz + rb[i] + 8)
                                    for sn in (sent_f, sent_b) for i, (f, _) in enumerate(lay)]),
-        "gather_codes_kernel": avg([sn[i] * (2 * rb[i] + 16 + 4)
+        "place_messages_kernel": avg([sn[i] * (2 * rb[i] + 16 + 4)
                                     for sn in (sent_f, sent_b) for i, (f, _) in enumerate(lay)]),
     }
     per_kernel = {}

@@ -169,8 +169,8 @@ int cdf_quantize(const void* cur, void* cached, const int32_t* idx, const int32_
                  int32_t max_sent, int32_t dim, int64_t ld, cdf_dtype dt, int bits, cdf_qscheme qs,
                  cdf_commit commit, int delta, uint8_t* codes, float* meta, void* stream);
 
-/* Host-side test hook: the number of polls after which a workgroup of the look-back route above gives
- * up waiting for its predecessors (polls <= 0 restores the default of about a million). */
+/* Host-side hook kept for callers that set it: no route of the message build waits for another workgroup, so
+ * the bound has nothing to act on. Accepts any value. */
 int cdf_set_message_wait_limit(int polls);
 
 /*
@@ -190,16 +190,11 @@ int cdf_dequantize(const uint8_t* codes, const float* meta, const int32_t* idx, 
 /*
  * cdf_cache_filter followed by cdf_quantize on the same rows, in one pass over them where that is
  * possible (quantised messages, ws of cdf_workspace_bytes(n_rows, dim, 0) or more):
- * a row is read once, tested, and - if it fails - coded and committed from the same registers.
- * Small inputs (all workgroups resident at once, some ten thousand rows) write every message
- * straight to its place: a workgroup learns the number of sent rows before its own from its
- * predecessors through status words in the workspace (single-pass scan with look-back; a workgroup
- * publishes its count before it waits, the wait is bounded). Larger inputs stage the messages by row
- * and move them into rank order with a second small kernel. In every other case the two calls run one
- * after the other. mask, idx, *n_sent, codes, meta and the committed cache are bit-identical to the
- * two calls on every route. Arguments as for those calls; capacity of idx / codes / meta = n_rows.
- * Should the bounded wait ever expire (never seen; it needs a workgroup that is not scheduled for
- * about a second), *n_sent is -1, which every consumer in this library treats as "no messages".
+ * a row is read once, tested, and - if it fails - coded and committed from the same registers. The
+ * messages are staged by row in the workspace and moved into rank order by a second kernel. In every
+ * other case the two calls run one after the other. mask, idx, *n_sent, codes, meta and the committed
+ * cache are bit-identical to the two calls on every route. Arguments as for those calls; capacity of
+ * idx / codes / meta = n_rows.
  */
 int cdf_cache_filter_quantize(const void* cur, void* cached, int32_t n_rows, int32_t dim, int64_t ld,
                               cdf_dtype dt, float eps, cdf_norm norm, int bits, cdf_qscheme qs,

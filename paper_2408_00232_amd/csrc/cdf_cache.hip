@@ -354,6 +354,13 @@ int scan_and_compact(const uint8_t* mask, int n_rows, int* counts, int* offsets,
   return CDF_OK;
 }
 
+// Exclusive offsets of per-block counts, their total in *n_sent.
+int scan_counts(const int* counts, int nblocks, int* offsets, int32_t* n_sent, hipStream_t st) {
+  { ProfScope ps(K_SCAN, st); scan_kernel<<<1, 1024, 0, st>>>(counts, nblocks, offsets, n_sent); }
+  CDF_LAUNCH_CHECK("scan");
+  return CDF_OK;
+}
+
 size_t filter_workspace_bytes(int64_t n_rows) {
   const int64_t nb = ceil_div(n_rows > 0 ? n_rows : 0, kRowsPerBlock);
   return align_up(static_cast<size_t>(scan_stride(nb) + nb + 1) * sizeof(int), 256);

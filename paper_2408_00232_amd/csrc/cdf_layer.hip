@@ -60,7 +60,7 @@ static const char* const kKernelNames[K_COUNT] = {
     "filter_kernel", "scan_kernel", "compact_kernel", "quantize_kernel", "dequantize_kernel",
     "chunk_rows_kernel", "spmm_fixup_kernel", "gemm_kernel<FWD>", "gemm_kernel<DW>",
     "reduce_slabs_kernel", "gemm_kernel<DM>", "spmm_walk_kernel", "relu_mask_kernel", "test_encode_kernel",
-    "gather_codes_kernel", "spmm_transform_kernel", "ordered_spmm_kernel"};
+    "place_messages_kernel", "spmm_transform_kernel", "ordered_spmm_kernel"};
 constexpr int kProfCap = 8192;
 struct ProfRec {
   int id;

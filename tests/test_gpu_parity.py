@@ -1134,6 +1134,33 @@ def test_cache_filter_quantize_equals_the_two_calls(dtype, dim, bits, qs, norm):
             assert (a == b) if isinstance(a, int) else torch.equal(a, b)
 
 
+@pytest.mark.parametrize("R", [1, 63, 64, 65, 131072, 131073, 262144, 262145])
+@pytest.mark.parametrize("dim,bits", [(3, 8), (5, 4), (15, 8), (16, 8), (37, 8), (64, 4)])
+def test_message_placement_at_block_and_row_edges(cdf, R, dim, bits):
+    """One call against cdf_cache_filter + cdf_quantize, bit for bit, around the block of 64 rows, the two ways to the
+    blocks' offsets (2048 blocks), the two block sizes (4096 blocks) and message rows of 3 to 37 bytes."""
+    gen = torch.Generator(device=DEV).manual_seed(R + dim)
+    cached0 = torch.randn(R, dim, generator=gen, device=DEV)
+    cur = cached0 * torch.where(torch.rand(R, 1, generator=gen, device=DEV) < 0.4, 1.5, 1.0)
+    rb = cdf.cdf_code_row_bytes(dim, bits, 0)
+    outs = []
+    for one in (True, False):
+        cached = cached0.clone()
+        mask, idx = torch.zeros(R, dtype=torch.uint8, device=DEV), torch.full((R,), -1, dtype=torch.int32, device=DEV)
+        n = torch.full((1,), -5, dtype=torch.int32, device=DEV)
+        codes, meta = torch.full((R * rb + 64,), 7, dtype=torch.uint8, device=DEV), torch.zeros(R, 2, device=DEV)
+        ws = ws_for(cdf, R, dim)
+        if one:
+            cdf.cdf_cache_filter_quantize(cur, cached, 0.05, 0, bits, 0, 1, True, mask, idx, n, codes, meta, ws)
+        else:
+            cdf.cdf_cache_filter(cur, cached, 0.05, 0, mask, idx, n, ws)
+            cdf.cdf_quantize(cur, cached, idx, n, R, bits, 0, 1, True, codes, meta)
+        torch.cuda.synchronize()
+        outs.append((n, mask, idx, codes, meta, cached))
+    for a, b in zip(*outs):     # what lies past the last message too: untouched
+        assert torch.equal(a, b)
+
+
 def test_look_back_wait_is_bounded(cdf, oracle):
     """The small-input route of cdf_cache_filter_quantize waits for its predecessors a bounded number of
     polls. With the bound forced down to one poll a call either completes as usual or reports -1 in
