@@ -23,6 +23,7 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0
 MFMA_PEAK_TFLOPS = {"f32": 157.3, "bf16": 2500.0}
 AGG_KERNELS = ("spmm_walk_kernel", "spmm_transform_kernel")
+SPLIT_AGG = "spmm_split_aggregation"   # all kernels of one aggregation of a matrix split by column class
 
 
 def log(*a):
@@ -195,7 +196,19 @@ def kernel_report(cdf, model, w, steps):
     per_step = [spmm_bytes(n, n + h, nnz, f, esz) for f in widths] + \
                [spmm_bytes(n + h, n, nnz, f, esz) for f in reversed(widths)]
     wid_of = list(widths) + list(reversed(widths))
-    agg = [(name, ms) for name, ms in seq if name in AGG_KERNELS]
+    # a matrix split by column class is one aggregation too: its preparation, two walks and the sum of the partial rows
+    # follow one another, and its time is that of them all
+    agg, split = [], None
+    for name, ms in seq:
+        if name == "split_kernels" and split is None:
+            split = 0.0
+        if split is not None:
+            split += ms
+            if name == "split_combine_kernel":
+                agg.append((SPLIT_AGG, split))
+                split = None
+        elif name in AGG_KERNELS:
+            agg.append((name, ms))
     nl = len(per_step)
     positions = None
     if len(agg) == nl * steps:

@@ -101,7 +101,9 @@ int cdf_profile_copy(void* dst, const void* src, size_t bytes, void* stream);
  * max_nnz stored entries. Host function, no device work. The figure includes the
  * row-indexed scratch (max_rows * (max_dim + 8) bytes) with which the layer steps test
  * and code the halo rows in one pass; a layer step given less than that, but at least its
- * own minimum, runs the two-pass route and produces the same bits. */
+ * own minimum, runs the two-pass route and produces the same bits. From 2^24 stored entries on it also
+ * includes what the aggregation by column class needs (max_rows * 12 + about max_nnz * 21 bytes; see
+ * cdf_spmm_fwd); with less the aggregation walks the matrix whole and its sums round differently. */
 size_t cdf_workspace_bytes(int64_t max_rows, int32_t max_dim, int64_t max_nnz);
 
 /* Bytes of one packed message row: dim*4 for CDF_Q_NONE, else ceil(dim*bits/8). The
@@ -215,7 +217,9 @@ int cdf_spmm_plan(const cdf_csr* A /* host */, int32_t* plan, size_t plan_bytes,
 /*
  * Aggregation over the normalised adjacency (Sec. 3.1, the product A^_i H of the forward
  * equation): Y[n_rows x dim] = A * X[n_cols x dim], fp32 accumulation in an order fixed by
- * the matrix shape alone (no atomics): bit-reproducible from run to run. `A` is a HOST pointer
+ * the matrix, dim and dt (no atomics): bit-reproducible from run to run. fp32 rows of 128 and more
+ * columns over 2^24 and more stored entries are summed by column class where ws holds the copies of the
+ * entries that this takes (cdf_workspace_bytes does), in another fixed order where it does not. `A` is a HOST pointer
  * to a struct of device arrays whose row pointers must be consistent (rowptr[n_rows] == nnz).
  * X and Y must not overlap. Empty rows give zero rows.
  */

@@ -9,6 +9,7 @@ namespace cdf {
 
 size_t filter_workspace_bytes(int64_t n_rows);
 size_t spmm_workspace_bytes(int64_t nnz, int32_t dim);
+size_t split_workspace_bytes(int64_t n_rows, int64_t nnz);
 size_t dense_workspace_bytes(int64_t n, int32_t f, int32_t g);
 size_t test_encode_workspace_bytes(int64_t n_rows, int32_t dim);
 int dense_fwd_ws(const void* M, int64_t ldm, cdf_dtype dt, const float* W, int32_t n, int32_t f_in, int32_t f_out,
@@ -60,7 +61,8 @@ static const char* const kKernelNames[K_COUNT] = {
     "filter_kernel", "scan_kernel", "compact_kernel", "quantize_kernel", "dequantize_kernel",
     "chunk_rows_kernel", "spmm_fixup_kernel", "gemm_kernel<FWD>", "gemm_kernel<DW>",
     "reduce_slabs_kernel", "gemm_kernel<DM>", "spmm_walk_kernel", "relu_mask_kernel", "test_encode_kernel",
-    "place_messages_kernel", "spmm_transform_kernel", "ordered_spmm_kernel"};
+    "place_messages_kernel", "spmm_transform_kernel", "ordered_spmm_kernel",
+    "split_kernels", "split_combine_kernel"};
 constexpr int kProfCap = 8192;
 struct ProfRec {
   int id;
@@ -160,7 +162,8 @@ extern "C" int cdf_profile_read_all(int32_t* kernel, float* ms, int cap) {
 extern "C" size_t cdf_workspace_bytes(int64_t max_rows, int32_t max_dim, int64_t max_nnz) {
   if (max_rows < 0 || max_dim <= 0 || max_nnz < 0) return 0;
   const size_t steps = filter_workspace_bytes(max_rows) +
-                       max_sz(spmm_workspace_bytes(max_nnz, max_dim), dense_workspace_bytes(max_rows, max_dim, max_dim));
+                       max_sz(spmm_workspace_bytes(max_nnz, max_dim) + split_workspace_bytes(max_rows, max_nnz),
+                              dense_workspace_bytes(max_rows, max_dim, max_dim));
   return max_sz(steps, test_encode_workspace_bytes(max_rows, max_dim));
 }
 

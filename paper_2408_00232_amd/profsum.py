@@ -181,6 +181,12 @@ def summarise(workload, order, d, out_dir):
                  f"their launches (scaled by the copy-kernel calibration: fetch x{fs:.3f}, write x{ws:.3f})\n")
         for b, (f, w) in per.items():
             fh.write(f"{b} = {mean(f):.0f} {(mean(w) if w else 0):.0f}\n")
+        # one aggregation of a matrix split by column class: its preparation, two walks, sum of the partial rows
+        n_split = len(per["split_combine_kernel"][0]) if "split_combine_kernel" in per else 0
+        if n_split and len(per["spmm_walk_kernel"][0]) == 2 * n_split:
+            parts = [v for b, v in per.items() if b == "spmm_walk_kernel" or b.startswith("split_")]
+            fh.write(f"spmm_split_aggregation = {sum(sum(f) for f, _ in parts) / n_split:.0f} "
+                     f"{sum(sum(w) for _, w in parts) / n_split:.0f}\n")
     return os.path.join(out_dir, f"layer_step_{workload}.md")
 
 

@@ -446,6 +446,50 @@ def test_spmm_run_borders_and_element_aligned_rows(cdf, oracle, dim, nnz_target,
     assert bool((yv[:, dim:] == 3.0).all()) and float(Yp[0]) == 3.0      # nothing outside the rows is written
 
 
+@pytest.mark.parametrize("rows,dim", [("mixed", 256), ("mixed", 242), ("short", 256), ("long", 256), ("even", 256)])
+def test_spmm_large_matrix_split_by_column_class(cdf, oracle, rows, dim):
+    """Aggregation of a matrix large enough for the column classes: rows at the edges of the long-row and unit lengths,
+    empty rows, one whose short part is empty, and two that stay whole (short rows; no column read more often than
+    another). The whole walk
+    (taken with a workspace too small for the copies) and sampled columns of the oracle are the references."""
+    pattern = {"mixed": [0, 1, 127, 128, 129, 0, 16384, 16385, 40000, 5, 300, 64, 0], "short": [20, 0, 21, 19] * 6 + [200],
+               "long": [128, 0, 0, 4096, 16385, 0], "even": [256, 3, 4096]}[rows]
+    rs = np.random.default_rng(dim)
+    lens = np.array(pattern * (17_000_000 // sum(pattern)) + [0, 0], np.int64)
+    rowptr = np.zeros(lens.size + 1, np.int64)
+    rowptr[1:] = np.cumsum(lens)
+    nnz, n_cols = int(rowptr[-1]), 1 << 20
+    assert nnz >= 1 << 24 and nnz * dim >= 4_000_000_000
+    colidx = rs.integers(0, n_cols, nnz, dtype=np.int32)
+    if rows != "even":
+        colidx[::3] = colidx[::3] & 1023        # hot columns
+    vals = rs.standard_normal(nnz, dtype=np.float32)
+    A = cdf.DeviceCsr(lens.size, n_cols, torch.from_numpy(rowptr), torch.from_numpy(colidx), torch.from_numpy(vals), DEV)
+    absA = cdf.DeviceCsr(lens.size, n_cols, torch.from_numpy(rowptr), torch.from_numpy(colidx),
+                         torch.from_numpy(np.abs(vals)), DEV)
+    gen = torch.Generator(DEV).manual_seed(dim)
+    X = torch.randn(n_cols, dim, device=DEV, generator=gen)
+    full = ws_for(cdf, n_cols, dim, nnz)
+    less = full[:full.numel() - 20 * nnz]       # the copies alone are 8 bytes an entry, the partial rows 12
+    Y, W, S = (torch.full((lens.size, dim + 2), 3.0, device=DEV) for _ in range(3))
+    cdf.cdf_spmm_fwd(A.struct, X, Y[:, :dim], full)
+    cdf.cdf_spmm_fwd(A.struct, X, W[:, :dim], less)
+    cdf.cdf_spmm_fwd(absA.struct, X.abs(), S[:, :dim], less)
+    torch.cuda.synchronize()
+    # every term passes through at most 128 additions of a run and 64 of runs, pieces, classes and units
+    bound = 192 * 2.0 ** -24 * S[:, :dim]
+    assert bool(((Y[:, :dim] - W[:, :dim]).abs() <= 2 * bound).all())
+    assert bool((Y[:, dim:] == 3.0).all())
+    cols = [0, 3, 4, 127, dim - 2, dim - 1]
+    want = as_f64(oracle.spmm(rowptr, colidx, vals, n_cols, to_np(X[:, cols].contiguous())))
+    assert (np.abs(as_f64(to_np(Y[:, cols].contiguous())) - want) <= as_f64(to_np(bound[:, cols].contiguous()))).all()
+    split = not torch.equal(Y[:, :dim], W[:, :dim])
+    assert split == (rows in ("mixed", "long"))
+    again = torch.full_like(Y, 3.0)
+    cdf.cdf_spmm_fwd(A.struct, X, again[:, :dim], full)
+    assert torch.equal(again, Y)
+
+
 @pytest.mark.parametrize("f_in,f_out", [(128, 16), (16, 8), (256, 41), (256, 47), (100, 47), (512, 24), (1024, 12),
                                         (64, 64), (4, 1), (256, 64), (128, 70), (37, 8)])
 @pytest.mark.parametrize("relu", [True, False])
