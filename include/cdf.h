@@ -101,7 +101,7 @@ int cdf_profile_copy(void* dst, const void* src, size_t bytes, void* stream);
  * max_nnz stored entries. Host function, no device work. The figure includes the
  * row-indexed scratch (max_rows * (max_dim + 8) bytes) with which the layer steps test
  * and code the halo rows in one pass; a layer step given less than that, but at least its
- * own minimum, runs the two-pass route and produces the same bits. From 2^24 stored entries on it also
+ * own minimum, runs the two-pass route and produces the same bits. From 128 columns and 2^24 stored entries on it also
  * includes what the aggregation by column class needs (max_rows * 12 + about max_nnz * 21 bytes; see
  * cdf_spmm_fwd); with less the aggregation walks the matrix whole and its sums round differently. */
 size_t cdf_workspace_bytes(int64_t max_rows, int32_t max_dim, int64_t max_nnz);
@@ -255,7 +255,9 @@ int cdf_spmm_dense_fwd(const cdf_csr* A /* host */, const void* X, int64_t ldx, 
  * Dense transform (Sec. 3.1: Z = (A^ H) W, H' = sigma(Z), sigma = ReLU or identity) on
  * the matrix cores. M [n x f_in] type dt, W [f_in x f_out] fp32 row-major,
  * Z (nullable), H (nullable) [n x f_out] fp32 row-major, contiguous.
- * fp32 M: fp32 matrix instructions. bf16 M with 16-byte aligned rows: bf16 matrix
+ * fp32 M: both operands split into three bf16 parts (24 bits of significand), the six products that reach
+ * 2^-24 of the result on the bf16 matrix instructions, high x high and the rest summed apart in fp32; results
+ * that are not finite that way are computed again with plain fp32 products. bf16 M with 16-byte aligned rows: bf16 matrix
  * instructions with W split into a bf16 high and low part (W = hi + lo up to 2^-17 |W|),
  * fp32 accumulation; other bf16 layouts widen M to fp32 on load.
  */
@@ -267,7 +269,7 @@ int cdf_dense_fwd(const void* M, int64_t ldm, cdf_dtype dt, const float* W, int3
  *   dZ = relu ? dH * [Zs > 0] : dH      (Zs: Z or H of the forward pass - same sign test)
  *   dW [f_in x f_out] fp32 = M^T dZ     (row blocks reduced in a fixed order: reproducible)
  *   dM [n x f_in] type dt  = dZ W^T     (skipped when dM is NULL)
- * fp32 matrix instructions, except for bf16 activations with 16-byte aligned W, dH, Zs: dM (f_out % 8
+ * fp32 operands are split in three as in cdf_dense_fwd. For bf16 activations with 16-byte aligned W, dH, Zs: dM (f_out % 8
  * == 0) on the bf16 matrix instructions with dZ and W each split into a bf16 high and low part (three
  * products, the low x low one dropped), fp32 accumulation, bf16 result; dW (f_in % 128 == 0, f_out %
  * 64 == 0, 16-byte aligned rows of M) likewise with dZ split in two (M is bf16 already).

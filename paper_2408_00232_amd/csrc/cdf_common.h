@@ -32,6 +32,8 @@ void set_error(const char* fmt, ...);
   } while (0)
 
 // ---- optional per-kernel timing (host side, HIP events on the launch stream) ----
+constexpr int kSplitColumns = 128;   // fewest columns for which the aggregation goes by column class
+
 enum KernelId {
   K_FILTER = 0, K_SCAN, K_COMPACT, K_QUANTIZE, K_DEQUANTIZE, K_SPMM_PLAN, K_SPMM_FIXUP,
   K_GEMM_FWD, K_GEMM_DW, K_GEMM_DW_REDUCE, K_GEMM_DM, K_SPMM_WALK, K_RELU_MASK, K_TEST_ENCODE, K_PLACE, K_SPMM_XFORM, K_SPMM_ORDERED, K_SPMM_SPLIT, K_SPMM_COMBINE,

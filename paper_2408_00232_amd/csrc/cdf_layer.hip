@@ -162,7 +162,8 @@ extern "C" int cdf_profile_read_all(int32_t* kernel, float* ms, int cap) {
 extern "C" size_t cdf_workspace_bytes(int64_t max_rows, int32_t max_dim, int64_t max_nnz) {
   if (max_rows < 0 || max_dim <= 0 || max_nnz < 0) return 0;
   const size_t steps = filter_workspace_bytes(max_rows) +
-                       max_sz(spmm_workspace_bytes(max_nnz, max_dim) + split_workspace_bytes(max_rows, max_nnz),
+                       max_sz(spmm_workspace_bytes(max_nnz, max_dim) +
+                                  (max_dim >= kSplitColumns ? split_workspace_bytes(max_rows, max_nnz) : 0),
                               dense_workspace_bytes(max_rows, max_dim, max_dim));
   return max_sz(steps, test_encode_workspace_bytes(max_rows, max_dim));
 }

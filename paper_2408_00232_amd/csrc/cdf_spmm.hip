@@ -1241,7 +1241,7 @@ __global__ __launch_bounds__(256) void split_combine_kernel(const int64_t* __res
 // 5.5 -> 5.0 and 4.0 -> 4.6 ms. The table of one line per row has to exceed what the L2s hold four times over and
 // more, and a column has to be read often; smaller work does not carry the dozen small launches (60 us).
 static bool split_pays(const cdf_csr* A, int dim) {
-  return dim >= 128 && A->nnz >= (int64_t(1) << 24) && A->nnz < (int64_t(1) << 31) - kSplitRows && A->nnz * dim >= int64_t(4000000000) &&
+  return dim >= kSplitColumns && A->nnz >= (int64_t(1) << 24) && A->nnz < (int64_t(1) << 31) - kSplitRows && A->nnz * dim >= int64_t(4000000000) &&
          static_cast<int64_t>(A->n_cols) * 128 >= (int64_t(128) << 20) && A->nnz >= 8 * static_cast<int64_t>(A->n_cols);
 }
 
