@@ -267,7 +267,8 @@ int cdf_dense_fwd(const void* M, int64_t ldm, cdf_dtype dt, const float* W, int3
 /*
  * Gradients of the dense transform (chain rule of Sec. 3.1 with sigma'(z) = [z > 0]):
  *   dZ = relu ? dH * [Zs > 0] : dH      (Zs: Z or H of the forward pass - same sign test)
- *   dW [f_in x f_out] fp32 = M^T dZ     (row blocks reduced in a fixed order: reproducible)
+ *   dW [f_in x f_out] fp32 = M^T dZ     (row blocks reduced in a fixed order: reproducible; fp32 M of few rows
+ *                                        takes shorter blocks where ws holds them)
  *   dM [n x f_in] type dt  = dZ W^T     (skipped when dM is NULL)
  * fp32 operands are split in three as in cdf_dense_fwd. For bf16 activations with 16-byte aligned W, dH, Zs: dM (f_out % 8
  * == 0) on the bf16 matrix instructions with dZ and W each split into a bf16 high and low part (three

@@ -445,16 +445,22 @@ __global__ __launch_bounds__(kReduceWaves * 64) void reduce_slabs_kernel(const f
 
 constexpr size_t kDwPartialCap = size_t(512) << 20;  // bytes of slab partials at most
 
-constexpr int kDwMinSlab = 256;  // rows per slab at least (a multiple of the k-tile)
+constexpr int kDwSlab = 256;     // rows per slab at least, where the slabs fill the chip that way
+constexpr int kDwMinSlab = 64;   // and otherwise (a multiple of the k-tile)
 
-static void dw_split(int n, int f, int g, int* slab_rows, int* slabs) {
-  int64_t rows = kDwMinSlab;
+// `fine`: slabs shorter than kDwSlab where a block could otherwise not be had for every CU. A slab is a serial loop over
+// its rows, 0.5 us and more per 32 of them (512 rows,
+// 128x16: 15.6 -> 10.3 us in slabs of 64 rows; 12500 rows, 256x41: 17 -> 12.9 us in slabs of 128); where the chip is full, the
+// partials' bytes cost more than shorter slabs save, hence the line at 256 blocks.
+static void dw_split(int n, int f, int g, bool fine, int* slab_rows, int* slabs) {
+  int64_t rows = kDwSlab;
   const size_t per = static_cast<size_t>(f) * g * sizeof(float);
   // enough blocks to fill the chip a few times over (tiles x slabs >= ~1500), not more
   const int64_t tiles = ceil_div(f, kBM) * ceil_div(g, g > 64 ? 128 : 64);
   // (both loops stop at one slab at the latest: rows >= n)
   while (rows < n && ceil_div(n, rows * 2) * tiles >= 1536) rows *= 2;
   while (rows < n && static_cast<size_t>(ceil_div(n, rows)) * per > kDwPartialCap) rows *= 2;
+  while (fine && rows > kDwMinSlab && ceil_div(n, rows / 2) * tiles <= 256) rows /= 2;
   *slab_rows = static_cast<int>(rows);
   *slabs = static_cast<int>(ceil_div(n > 0 ? n : 1, rows));
 }
@@ -564,8 +570,14 @@ int dense_bwd_ws(const void* M, int64_t ldm, cdf_dtype dt, const float* W, const
                   aligned(dM, esz),
               "cdf_dense_bwd: misaligned pointer");
   int slab_rows, slabs;
-  dw_split(n, f_in, f_out, &slab_rows, &slabs);
-  const size_t need = align_up(static_cast<size_t>(slabs) * f_in * f_out * sizeof(float), 256);
+  size_t need = 0;
+  // a workspace for slabs of kDwSlab rows is accepted too (and bf16 activations keep those: their results are the same
+  // bits whatever the workspace)
+  for (int fine = dt == CDF_F32 ? 1 : 0; fine >= 0; --fine) {
+    dw_split(n, f_in, f_out, fine != 0, &slab_rows, &slabs);
+    need = align_up(static_cast<size_t>(slabs) * f_in * f_out * sizeof(float), 256);
+    if (ws_bytes >= need) break;
+  }
   if (!ws || !aligned(ws, 16) || ws_bytes < need)
     CDF_FAIL(CDF_ERR_WORKSPACE, "cdf_dense_bwd: workspace too small (%zu < %zu)", ws_bytes, need);
   float* part = static_cast<float*>(ws);

@@ -1003,6 +1003,27 @@ def test_backward_with_recovered_commit_keeps_its_order_of_summation(cdf, f_in, 
         assert bool(((x - y).abs() <= 512 * 2.0 ** -24 * scale + 2 * step * scale).all())
 
 
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 127, 129, 512, 1000])
+@pytest.mark.parametrize("f,g,dtype", [(128, 16, torch.float32), (37, 41, torch.float32), (256, 300, torch.float32),
+                                       (128, 64, torch.bfloat16)])
+def test_dense_dw_short_row_slabs(cdf, n, f, g, dtype):
+    """dW of few rows, in slabs of 64 rows and up (fp32): against 64 bits, with the declared workspace and with one that only
+    holds slabs of 256 rows."""
+    gen = torch.Generator().manual_seed(n + f)
+    M = torch.randn(n, f, generator=gen).to(dtype).to(DEV)
+    W = torch.randn(f, g, generator=gen).to(DEV)
+    Zs, dH = (torch.randn(n, g, generator=gen).to(DEV) for _ in range(2))
+    dz = torch.where(Zs > 0, dH, torch.zeros_like(dH)).double()
+    want, size = M.double().t() @ dz, M.double().abs().t() @ dz.abs()
+    coarse = (-(-n // 256) * f * g * 4 + 255) // 256 * 256
+    for ws in (ws_for(cdf, n, max(f, g)), torch.zeros(coarse, dtype=torch.uint8, device=DEV)):
+        dW = torch.full((f, g), 3.0, device=DEV)
+        cdf.cdf_dense_bwd(M, W, Zs, dH, True, dW, None, ws)
+        # fp32: products exact to 2^-23, one rounding per 16 rows and per slab; bf16: dZ in two parts, 2^-16
+        bound = ((n / 8 + 32) * 2.0 ** -24 + (2.0 ** -16 if dtype == torch.bfloat16 else 0.0)) * size
+        assert bool(((dW.double() - want).abs() <= bound).all())
+
+
 @pytest.mark.parametrize("n,classes", [(1000, 8), (777, 41), (300, 64), (130, 47), (64, 1), (500, 200)])
 def test_softmax_xent(cdf, oracle, n, classes):
     g = torch.Generator().manual_seed(n + classes)
